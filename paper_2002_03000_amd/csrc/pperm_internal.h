@@ -22,9 +22,11 @@ enum : uint32_t { CTRL_QUEUE = 0, CTRL_ERR = 1, CTRL_WORDS = 16 };
 // Modes (same values as the ABI).
 enum : uint32_t { MODE_SHARED = 0, MODE_INDEPENDENT = 1, MODE_ROSENBLUTH = 2 };
 
-// Longest cubic walk whose sites are keyed in 32 bits (10 bits per coordinate
-// modulo 1024, see Lat3c): n_max + 1 < 1024.
-constexpr uint32_t COMPACT3_MAX_N = 1022;
+// Cubic walks up to COMPACT3_MAX_N steps key a site (x, y, z) in 32 bits as
+// x + SITE3_Y y + SITE3_Z z + SITE3_0 (see Site3c, where the limit comes from).
+constexpr uint32_t COMPACT3_MAX_N = 2063;
+constexpr uint32_t SITE3_0 = 0x8636F212u, SITE3_Y = 0x4A43C99Cu, SITE3_Z = 0x555C468Fu;
+constexpr uint32_t SITE3_Z_INV = 0x73A0186Fu;   // SITE3_Z * SITE3_Z_INV = 1 modulo 2^32
 
 constexpr int STATS_WORDS = 10;
 constexpr uint32_t GROUPS = 16;   // sequence groups of the error estimate (s mod 16)

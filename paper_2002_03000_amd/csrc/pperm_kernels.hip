@@ -8,19 +8,17 @@
 // one 64-lane wavefront takes one (problem, sequence) item at a time from a
 // device queue and runs that sequence's tours; every walk quantity is uniform
 // over the wave, and the lanes split the parallel parts of a step:
-//   - the occupancy scan: lane (dir, off) reads slot home(dir)+off+W*round of
-//     the walk's open-addressing table, so the 2d neighbours and W consecutive
-//     probe positions per neighbour are looked up in one LDS instruction and
-//     resolved with two wave ballots;
+//   - the occupancy scan: lane (dir, o) reads the slot that neighbour dir has in
+//     subtable o of the walk's table, so all neighbours are looked up in all
+//     their places in one LDS instruction and resolved with two wave ballots;
 //   - the random numbers: lane i computes the Philox4x32-10 block of event
 //     k0+i, so one pass of the (quarter-rate) multiplies serves 64 events;
 //   - the LIFO deletion of abandoned sites after a backtrack.
-// The walk's occupancy table (packed coordinates, linear probing, restored
-// exactly by LIFO deletion through remembered slot ids), the slot ids and the
-// sequence's own per-length sums live in LDS (the sums in global memory for
-// long walks); the 64 most recent pending copies live in the lanes of a few
-// vector registers; the pooled sums are read with scalar loads.  A second kernel
-// (run_kernel) packs 64/TS walks into a wave as teams of TS lanes.
+// The walk's occupancy table (one key per site, restored exactly by LIFO
+// deletion through remembered slot ids), the slot ids and the sequence's own
+// per-length sums live in LDS (the sums in global memory for long walks); the
+// 64 most recent pending copies live in the lanes of a few vector registers.  A
+// second kernel (run_kernel) packs 64/TS walks into a wave as teams of TS lanes.
 //
 // Determinism.  Every floating-point decision uses the same IEEE operations
 // in the same order as the reading of the method these kernels implement
@@ -131,23 +129,25 @@ __device__ __forceinline__ XF xf_add_nz(XF a, XF b) {
 }
 
 // x / y, correctly rounded, for operands whose quotient and reciprocal are
-// far from the ends of the FP64 range: x in [0.5, 1) and y in [0.5, 2^34]
-// here (a mantissa, or a mantissa over an integer below 2^34).  Markstein's
-// method: the hardware reciprocal refined by two Newton-Raphson steps with
-// fused multiply-adds, the quotient x * y, and one correction with the exact
-// residual x - y q.  It is the general IEEE division sequence without its
-// operand scaling and special-case fix-up, which leave such operands and
-// their quotient unchanged.
-__device__ __forceinline__ double div_normal(double x, double y) {
+// far from the ends of the FP64 range.  Markstein's method: the hardware
+// reciprocal refined by two Newton-Raphson steps with fused multiply-adds, the
+// quotient x * y, and one correction with the exact residual x - y q.  It is
+// the general IEEE division sequence without its operand scaling and
+// special-case fix-up, which leave such operands and their quotient unchanged.
+__device__ __forceinline__ double recip_normal(double y) {
     double r = __builtin_amdgcn_rcp(y);
     double e = __builtin_fma(-y, r, 1.0);
     r = __builtin_fma(r, e, r);
     e = __builtin_fma(-y, r, 1.0);
-    r = __builtin_fma(r, e, r);
+    return __builtin_fma(r, e, r);
+}
+// x / y given r = recip_normal(y)
+__device__ __forceinline__ double div_by(double x, double y, double r) {
     const double q = x * r;
     const double res = __builtin_fma(-y, q, x);
     return __builtin_fma(res, r, q);
 }
+__device__ __forceinline__ double div_normal(double x, double y) { return div_by(x, y, recip_normal(y)); }
 
 __device__ __forceinline__ XF xf_mul_nz(XF a, double k) { return xf_norm_nz(a.m * k, a.e); }
 // a / k for an integer 2 <= k < 2^34
@@ -171,17 +171,7 @@ __device__ __forceinline__ XF xf_of(const SumRec& r) { return XF{r.m, r.e}; }
 template <int D> struct Lat;
 template <> struct Lat<2> {
     using Key = uint32_t;
-    static constexpr int D = 2;
     static constexpr int DP = 4;  // direction lanes per probe window
-    __device__ static Key origin() { return pack(0, 0, 0); }
-    // neighbour key = end key + delta(dir): no field ever carries, every
-    // coordinate stays within +-n_max < 2^15 of its 2^15 offset
-    __device__ static Key delta(int dir) {
-        if (dir >= 4) return 0u;
-        const Key mag = (Key)1 << (16 * (dir >> 1));
-        return (dir & 1) ? (Key)((Key)0 - mag) : mag;
-    }
-    __device__ static Key next(Key k, Key d) { return k + d; }
     __device__ static Key pack(int x, int y, int) {
         return (uint32_t)(x + 32768) | ((uint32_t)(y + 32768) << 16);
     }
@@ -194,15 +184,7 @@ template <> struct Lat<2> {
 };
 template <> struct Lat<3> {
     using Key = uint64_t;
-    static constexpr int D = 3;
     static constexpr int DP = 8;
-    __device__ static Key origin() { return pack(0, 0, 0); }
-    __device__ static Key delta(int dir) {
-        if (dir >= 6) return 0u;
-        const Key mag = (Key)1 << (16 * (dir >> 1));
-        return (dir & 1) ? (Key)((Key)0 - mag) : mag;
-    }
-    __device__ static Key next(Key k, Key d) { return k + d; }
     __device__ static Key pack(int x, int y, int z) {
         return (uint64_t)(uint32_t)(x + 32768) | ((uint64_t)(uint32_t)(y + 32768) << 16) |
                ((uint64_t)(uint32_t)(z + 32768) << 32);
@@ -217,34 +199,6 @@ template <> struct Lat<3> {
     }
 };
 
-// The cubic lattice for walks of at most COMPACT3_MAX_N steps, with 32-bit
-// keys: each coordinate modulo 1024 in a 10-bit field (x in bits 0-9, y in
-// 11-20, z in 22-31) with a zero guard bit between fields, the origin at 512
-// in every field.  Any two sites of one walk, and a site of the walk and a
-// neighbour of its end, differ by at most n_max + 1 <= 1023 in every
-// coordinate, so their keys differ; key 0 would need |x| + |y| + |z| >= 1536.
-// A neighbour's key is the end's key plus a per-direction offset (-1 is +1023
-// in the field), with the carry out of a field dropped at its guard bit.
-struct Lat3c {
-    static constexpr int D = 3;
-    using Key = uint32_t;
-    static constexpr uint32_t GUARD = (1u << 10) | (1u << 21);
-    __device__ static Key origin() { return 512u | (512u << 11) | (512u << 22); }
-    // offset of direction dir (+x, -x, +y, -y, +z, -z); 0 past the six
-    __device__ static Key delta(int dir) {
-        if (dir >= 6) return 0u;
-        const uint32_t sh = 11u * (uint32_t)(dir >> 1);
-        return (dir & 1) ? (1023u << sh) : (1u << sh);
-    }
-    __device__ static Key next(Key k, Key d) { return (k + d) & ~GUARD; }
-    __device__ static uint32_t hash(Key k) { return k * 0x9E3779B1u; }
-};
-
-// The lattice (key format) a walker instance uses: packed int16 coordinates,
-// or the compact cubic keys above.
-template <int D, bool CK> struct LatOf { using T = Lat<D>; };
-template <> struct LatOf<3, true> { using T = Lat3c; };
-
 __device__ __forceinline__ int dir_dx(int d) { return (d == 0) - (d == 1); }
 __device__ __forceinline__ int dir_dy(int d) { return (d == 2) - (d == 3); }
 __device__ __forceinline__ int dir_dz(int d) { return (d == 4) - (d == 5); }
@@ -253,6 +207,10 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
+
+// Compile-time switches of a generic lambda.
+struct yes { static constexpr bool value = true; };
+struct no { static constexpr bool value = false; };
 
 // Team phases.
 enum : int { PH_NEED_SEQ = 0, PH_NEED_TOUR = 1, PH_NEED_BT = 2, PH_AT_NODE = 3, PH_DONE = 4,
@@ -631,17 +589,6 @@ __global__ void __launch_bounds__(64) run_kernel(RunArgs A) {
 // with scalar loads, and each pending-copy entry carries its endpoint site, so
 // a backtrack needs no table lookup to restore the walk's end.
 // ---------------------------------------------------------------------------
-// OR of v over aligned groups of G lanes (G = 8 or 16), every lane of a group
-// receiving the group's OR: DPP quad permutes, then half-row and row mirrors.
-template <int G>
-__device__ __forceinline__ uint32_t group_or(uint32_t v) {
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
-    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);  // row_half_mirror
-    if (G == 16) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false);  // row_mirror
-    return v;
-}
-
 __device__ __forceinline__ uint32_t ufirst(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int ufirst_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint64_t ufirst64(uint64_t v) {
@@ -704,33 +651,172 @@ __device__ __forceinline__ void store_global(T* p, const T& v) {
     for (size_t i = 0; i < sizeof(T) / 4; ++i) q[i] = d[i];
 }
 
-// Direction sets of one probe window as 64-bit lane masks: direction d owns
-// lanes [d*W, d*W + W); a set of directions is kept as the top bit of each
-// owned field (FHI), so that "does any lane of this direction show X" is a
-// field-wise nonzero test on the ballot of X.
-template <int D> struct Fields;
-template <> struct Fields<2> {
-    static constexpr int W = 16, LW = 4;
-    static constexpr uint64_t HI = 0x8000800080008000ull, LO = 0x7FFF7FFF7FFF7FFFull;
-};
-template <> struct Fields<3> {
-    static constexpr int W = 8, LW = 3;
-    static constexpr uint64_t HI = 0x0000808080808080ull, LO = 0x00007F7F7F7F7F7Full;
+// ---------------------------------------------------------------------------
+// Sites of the wave walker.  A site's key is a linear function of its
+// coordinates (modulo 2^32 per word), so a neighbour's key is the end's key
+// plus a per-direction offset, and no key a walk can meet is 0 (an empty slot).
+// word(): the 32-bit word that is hashed.
+// ---------------------------------------------------------------------------
+struct Site2 {
+    using Key = uint32_t;               // x + 2^16 y + origin; coordinates stay below 2^15
+    __device__ static Key origin() { return 0x80008000u; }
+    __device__ static Key delta(int dir) {
+        if (dir >= 4) return 0u;
+        const Key mag = (dir >> 1) ? 0x10000u : 1u;
+        return (dir & 1) ? 0u - mag : mag;
+    }
+    __device__ static Key next(Key k, Key d) { return k + d; }
+    __device__ static uint32_t word(Key k) { return k; }
+    __device__ static bool empty(Key k) { return k == 0u; }
+    __device__ static uint32_t mark(Key k) { return k; }      // nonzero iff a site
+    __device__ static void unpack(Key k, int& x, int& y, int& z) {
+        x = (int)(k & 0xFFFFu) - 32768;
+        y = (int)(k >> 16) - 32768;
+        z = 0;
+    }
 };
 
-// Top bit of every field of x that has any bit set (fields never carry into
-// each other: (2^(W-1) - 1) * 2 < 2^W).
-template <int D>
-__device__ __forceinline__ uint64_t fields_any(uint64_t x) {
-    using F = Fields<D>;
-    return (((x & F::LO) + F::LO) | x) & F::HI;
+// Cubic walks of at most COMPACT3_MAX_N steps: x + SITE3_Y y + SITE3_Z z +
+// SITE3_0 modulo 2^32.  The shortest nonzero step (in the sum of |coordinate|)
+// with the same key as no step at all is 2293 long and the shortest that takes
+// the origin's key to 0 is 2065 long (both checked exhaustively by
+// tests/test_walker_keys.py), while two sites of one walk, or a site and a neighbour of
+// its end, are at most n_max + 1 <= 2064 apart.
+struct Site3c {
+    using Key = uint32_t;
+    __device__ static Key origin() { return SITE3_0; }
+    __device__ static Key delta(int dir) {
+        if (dir >= 6) return 0u;
+        const int axis = dir >> 1;
+        const Key mag = axis == 0 ? 1u : axis == 1 ? SITE3_Y : SITE3_Z;
+        return (dir & 1) ? 0u - mag : mag;
+    }
+    __device__ static Key next(Key k, Key d) { return k + d; }
+    __device__ static uint32_t word(Key k) { return k; }
+    __device__ static bool empty(Key k) { return k == 0u; }
+    __device__ static uint32_t mark(Key k) { return k; }
+};
+
+// Every other cubic walk: that key in the low word and the square-lattice key
+// of (x, y) in the high word, which is never 0.  Equal keys have equal x and y,
+// and SITE3_Z is odd, so z is equal too.
+struct Site3 {
+    using Key = uint64_t;
+    __device__ static Key join(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
+    __device__ static Key origin() { return join(SITE3_0, 0x80008000u); }
+    __device__ static Key delta(int dir) { return join(Site3c::delta(dir), Site2::delta(dir)); }
+    __device__ static Key next(Key k, Key d) {
+        return join((uint32_t)k + (uint32_t)d, (uint32_t)(k >> 32) + (uint32_t)(d >> 32));
+    }
+    __device__ static uint32_t word(Key k) { return (uint32_t)k; }
+    __device__ static bool empty(Key k) { return (uint32_t)(k >> 32) == 0u; }
+    __device__ static uint32_t mark(Key k) { return (uint32_t)(k >> 32); }
+    __device__ static void unpack(Key k, int& x, int& y, int& z) {
+        Site2::unpack((uint32_t)(k >> 32), x, y, z);
+        // SITE3_Z * z, divided by SITE3_Z modulo 2^32
+        z = (int)(((uint32_t)k - SITE3_0 - (uint32_t)x - SITE3_Y * (uint32_t)y) * SITE3_Z_INV);
+    }
+};
+
+template <int D, bool CK> struct SiteOf { using T = Site2; };
+template <> struct SiteOf<3, false> { using T = Site3; };
+template <> struct SiteOf<3, true> { using T = Site3c; };
+
+// Set bits of m, counted on the vector side: a lane mask that a vector compare
+// wrote costs the scalar unit a wait of some 16 cycles before it can read it.
+// (The two wait states are the hardware's between a vector instruction that
+// writes a scalar register and one that reads it.)
+__device__ __forceinline__ uint32_t mask_count(uint64_t m) {
+    uint32_t r;
+    asm("s_nop 1\n\t"
+        "v_bcnt_u32_b32 %0, %1, 0\n\t"
+        "v_bcnt_u32_b32 %0, %2, %0"
+        : "=&v"(r) : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)));
+    return r;
 }
 
-// Every lane of the fields whose top bit is set in hb.
-template <int D>
-__device__ __forceinline__ uint64_t fields_lanes(uint64_t hb) {
-    const uint64_t x = hb >> (Fields<D>::W - 1);
-    return (x << Fields<D>::W) - x;
+// The smaller of two numbers, without the compiler's NaN quieting around it (a
+// NaN operand gives the other one, two of them a NaN).
+__device__ __forceinline__ double min_f64(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(T* p) {
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)p;
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <typename T>
+__device__ __forceinline__ T lds_load(uint32_t address) {
+    return *(const __attribute__((address_space(3))) T*)(uintptr_t)address;
+}
+// A record read whole through a word vector.
+__device__ __forceinline__ SumRec record_of(u32x4 w) {
+    SumRec r;
+    r.m = __builtin_bit_cast(double, ((uint64_t)w.y << 32) | w.x);
+    r.e = (int32_t)w.z;
+    r.h = w.w;
+    return r;
+}
+__device__ __forceinline__ u32x4 words_of(double m, int32_t e, uint32_t h) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, m);
+    u32x4 r;
+    r.x = (uint32_t)b;
+    r.y = (uint32_t)(b >> 32);
+    r.z = (uint32_t)e;
+    r.w = h;
+    return r;
+}
+
+// One arrival's writes, by lane `il` alone: the site's key into its table slot,
+// its slot id, and the record of its length (in LDS, or with LONG in global
+// memory).  taddr: the slot's LDS address in lane il; saddr, raddr: the slot-id
+// and record addresses of the length before.  One lane selected with a scalar
+// shift takes two instructions; a compare and a saved mask would take six.
+template <bool LONG>
+__device__ __forceinline__ void write_arrival(uint32_t il, uint32_t taddr, uint32_t key, uint32_t saddr,
+                                              uint32_t slot, uint32_t raddr, u32x4 rec, const void* gbase) {
+    if constexpr (LONG)
+        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                     "ds_write_b32 %1, %2\n\t"
+                     "ds_write_b16 %3, %4 offset:2\n\t"
+                     "s_nop 1\n\t"
+                     "global_store_dwordx4 %5, %6, %7 offset:16\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec), "s"(gbase)
+                     : "memory", "scc");
+    else
+        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                     "ds_write_b32 %1, %2\n\t"
+                     "ds_write_b16 %3, %4 offset:2\n\t"
+                     "ds_write_b128 %5, %6 offset:16\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec)
+                     : "memory", "scc");
+}
+template <bool LONG>
+__device__ __forceinline__ void write_arrival(uint32_t il, uint32_t taddr, uint64_t key, uint32_t saddr,
+                                              uint32_t slot, uint32_t raddr, u32x4 rec, const void* gbase) {
+    if constexpr (LONG)
+        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                     "ds_write_b64 %1, %2\n\t"
+                     "ds_write_b16 %3, %4 offset:2\n\t"
+                     "s_nop 1\n\t"
+                     "global_store_dwordx4 %5, %6, %7 offset:16\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec), "s"(gbase)
+                     : "memory", "scc");
+    else
+        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                     "ds_write_b64 %1, %2\n\t"
+                     "ds_write_b16 %3, %4 offset:2\n\t"
+                     "ds_write_b128 %5, %6 offset:16\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec)
+                     : "memory", "scc");
 }
 
 // One sequence's `tours` tours against frozen pooled sums (the whole hot path
@@ -738,15 +824,27 @@ __device__ __forceinline__ uint64_t fields_lanes(uint64_t hb) {
 // problem's own, or an epoch's copy in a chained launch); fresh: the epoch
 // starts here, so the sequence's sums and tour count start from zero instead
 // of being read.  Returns the tours run, with bit 31 set if the step cap
-// stopped the sequence (WALK_ABORTED).  Every value below is wave-uniform
-// except where a lane index enters (scan windows, Philox counters, deletions).
-// A step issues its occupancy reads first, evaluates the prune/enrich
-// arithmetic while they are in flight, and only then resolves the scan.
+// stopped the sequence (WALK_ABORTED).
 // OBS: also record W * R^2 (squared end-to-end distance) at every arrival
 // beside the weight, the numerator of the ratio estimator of eqn (5).
 // LONG: walks too long for the per-length sums to share LDS with the
 // occupancy table; the sums stay in the sequence's global row (read and
-// written in place) and LDS holds the table, the slot ids and the stack bottom.
+// written in place) and LDS holds the table and the slot ids.
+//
+// What bounds it.  Every step depends on the one before, and a lone wave issues
+// an instruction every 4.3 cycles whatever it is (dependent FP64 included), so
+// a walk-step costs its instruction count, plus what crosses units: 12 cycles
+// for a branch not taken, 20 for one taken, 16 where the scalar unit reads what
+// the vector unit wrote.  So the common event -- a walk with a free neighbour,
+// a decision that keeps one copy (or a survivor), a growth that ends neither
+// the walk, the random block nor the step budget -- is one straight block of
+// vector code with a single loop branch (run_ahead), and everything else is
+// found by that block's one test and handled outside it (see the event loop).
+// Before, with every case decided in line (255 instructions and 17 branches a
+// step): one square sequence of 20-step walks, 1000 tours, 12.36 ms, now 8.42;
+// 4096 square sequences of 500 steps, 64 tours, 94.7 ms, now 70.2; 16384 cubic
+// ones of 1000 steps, 32 tours, 205 ms, now 149; 256 Rosenbluth walks of up to
+// 6000 cubic steps, twice, 6.40 ms, now 3.40.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 
 template <int D, bool OBS = false, bool LONG = false, bool CK = false>
@@ -754,11 +852,13 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
                                                   uint32_t s, unsigned char* lds, const SumRec* Gsrc,
                                                   bool fresh) {
     static_assert(!(OBS && CK), "observables need coordinates, which compact keys do not keep");
-    using L_ = typename LatOf<D, CK>::T;
-    using Key = typename L_::Key;
-    using F = Fields<D>;
-    constexpr int W = F::W;                    // probe positions per direction per window
-    constexpr uint32_t FIELD = (1u << W) - 1u;
+    using S_ = typename SiteOf<D, CK>::T;
+    using Key = typename S_::Key;
+    constexpr int W = (D == 2) ? 16 : 8;       // lanes per direction
+    constexpr int LW = (D == 2) ? 4 : 3;
+    constexpr uint64_t FIELD = (1ull << W) - 1ull;
+    // the last lane of every direction
+    constexpr uint64_t BLANK = (D == 2) ? 0x8000800080008000ull : 0x0000808080808080ull;
 
     // LDS: the occupancy table, the slot id of every site of the walk and the
     // sequence's own per-length sums (moved in at the start of the sequence's
@@ -780,44 +880,53 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
         else *p = v;
     };
     const int lane = (int)threadIdx.x;
-    // S slots, a power of two or 1.5 times one: the home slot of a key is the
-    // high word of hash * S (for S = 2^b the top b bits of the hash), and a
-    // probe position past the end wraps by one subtraction (min(x, x - S) on
-    // unsigned values: positions stay below 2S)
     const uint32_t S = P.slots;
-    auto wrap = [S](uint32_t x) { return __builtin_elementwise_min(x, x - S); };
 
-    // probe-lane role: direction-major, W lanes per direction (lanes past the
-    // 2d directions read a slot that no mask ever selects)
-    const int pdir = lane / W;
+    // The occupancy table is W - 1 subtables of `sub` slots.  A site may sit in
+    // one slot of each, found by a hash of its own per subtable, and takes the
+    // first that is empty: lane dir * W + o reads the slot of neighbour dir in
+    // subtable o, so one LDS read looks a step's neighbours up in all their
+    // places, a neighbour is occupied iff one of its lanes reads its key, and
+    // lanes below a hit are always occupied (deletion is last in, first out).
+    // At load 0.5 a walk of 1000 cubic steps finds its places all taken about
+    // once in 10^4 walks (linear probing over the same lanes: ten times per
+    // walk), and 0.65 still costs under 0.3% of its steps; such a site goes into
+    // any empty slot, and far_lo tells the scan to look for it (below).  The
+    // last lane of a direction, and the lanes past the directions, read slot
+    // S - 1, which no subtable holds (S is 2^b or 3 * 2^b, never a multiple of
+    // W - 1) and which stays empty: a free direction has a lane that reads an
+    // empty slot even when its places are taken.
+    // (lanes past the directions: never chosen, whatever is occupied)
+    const int pdir = lane / W < 2 * D ? lane / W : 64;
     const int poff = lane % W;
-    // The walk's end is carried as its packed key; a neighbour's key is the
-    // end's key moved by a per-direction offset (L_::next).  Direction 2i
-    // steps +1 along axis i, direction 2i+1 steps -1; lanes past the 2d
-    // directions get offset 0 (the end itself) and are never selected.
-    const Key pdelta = L_::delta(pdir);
-    // A zero the compiler cannot see through.  Indexing the per-length records
-    // with it keeps the weight arithmetic in vector registers (the walk's
-    // control state stays scalar) and lets the record read overlap the step
-    // instead of being waited for on the spot to move it to scalar registers.
+    const uint32_t sub = S / (uint32_t)(W - 1);
+    const bool blank = poff == W - 1 || pdir >= 2 * D;
+    const uint32_t lane_sub = blank ? 0u : sub;
+    const uint32_t lane_base = blank ? S - 1u : (uint32_t)poff * sub;
+    const uint32_t lane_mul = ((0x9E3779B1u * (uint32_t)(poff + 1)) ^ (0x85EBCA77u * (uint32_t)(poff + 3))) | 1u;
+    const Key pdelta = S_::delta(pdir);
+    auto slot_of = [&](Key k) { return __umulhi(S_::word(k) * lane_mul, lane_sub) + lane_base; };
+
+    // A zero the compiler cannot see through: addresses and sums formed with it
+    // stay in vector registers.
     uint32_t vz;
     asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
 
     const uint32_t n_max = P.n_max;
     const uint32_t row = P.row;
     const bool shared_mode = (P.mode == MODE_SHARED);
-    const uint32_t control_mode = (P.mode != MODE_ROSENBLUTH) ? 1u : 0u;
+    const bool control_mode = (P.mode != MODE_ROSENBLUTH);
     const double pool = shared_mode ? (double)P.N : 1.0;
     const uint64_t pool_u = shared_mode ? (uint64_t)P.N : 1ull;
 
     // the empty table with the origin in it, slot id of site 0
     for (uint32_t i = (uint32_t)lane; i < S; i += 64) table[i] = (Key)0;
     wave_fence();
-    const Key origin_key = L_::origin();
-    const uint32_t origin_slot = __umulhi(L_::hash(origin_key), S);
-    if (lane == 0) {
-        table[origin_slot] = origin_key;
-        sid[0] = (uint16_t)origin_slot;
+    const Key origin_key = S_::origin();
+    if (lane == 0) {                           // (lane 0: subtable 0)
+        const uint32_t o = slot_of(origin_key);
+        table[o] = origin_key;
+        sid[0] = (uint16_t)o;
     }
     wave_fence();
 
@@ -827,7 +936,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
 
     const size_t rb0 = (size_t)s * row;
     SumRec* __restrict__ Lrow = P.L + rb0;
-    const SumRec* Grow = shared_mode ? Gsrc : Gsrc + rb0;   // read with load_const
+    const SumRec* Grow = shared_mode ? Gsrc : Gsrc + rb0;
     if (!shared_mode) MGs = ufirst64(P.MG[s]);
     const uint64_t t0 = ufirst64(P.t[s]);
     uint32_t tlo = (uint32_t)t0;               // tour index: its low word keys the random numbers
@@ -857,9 +966,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     // (lane i accumulates statistics word i)
     uint32_t c_steps = 0, c_tours = 0, c_maxd = 0;
     const uint32_t capv = cap ? cap : 0xFFFFFFFFu;   // step cap of this call (0: none)
-    uint64_t c_events = 0;                     // events: the sum over tours of k
+    uint64_t c_events = 0;                     // events: the sum over tours of kb + li
     uint64_t cv = 0;
-    uint32_t digest = (uint32_t)ufirst64(P.stats[(size_t)s * STATS_WORDS + ST_DIGEST]);
+    uint32_t digest = (uint32_t)P.stats[(size_t)s * STATS_WORDS + ST_DIGEST] + vz;
     bool abort = false;
     // the registers of the copy stack (see the tour loop)
     uint32_t cs_n = 0u, cs_rem = 0u;
@@ -867,243 +976,348 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     double cs_m = 0.0;
     Key cs_key = (Key)0;
 
+    // byte addresses of length 0: its record (in LDS, or with LONG as an offset
+    // from the row) and its slot id; gsums + a record's address is the pooled
+    // sum of the same length
+    const uint32_t rec_base = LONG ? 0u : lds_address(Ls);
+    const uint32_t sid_base = lds_address(sid);
+    const unsigned char* gsums = reinterpret_cast<const unsigned char*>(Grow) - rec_base;
+    auto pooled = [&](uint32_t address) {
+        return load_global(reinterpret_cast<const SumRec*>(gsums + address));
+    };
+
     for (uint32_t tour = 0; tour < tours && !abort; ++tour) {
         // ---- a pass through the empty walk (eqn (4), M) ----
         const uint32_t tt = tlo;
         tlo += 1u;
         m += 1;
         c_tours += 1;
-        XF w = {0.5, 1};                       // W_0 = 1
         {
-            const XF r0 = xf_add(xf_of(rec0), w);
+            const XF r0 = xf_add(xf_of(rec0), XF{0.5, 1});   // W_0 = 1
             rec0.m = r0.m;
             rec0.e = r0.e;
             rec0.h += 1u;
         }
-        // events of this tour; fewer than 2^32 because the step cap is at most
-        // 2^31 and every event either grows the walk or prunes a grown copy
-        // (kb starts 64 below k, so the first event computes a block)
-        uint32_t k = 0, kb = (uint32_t)-64;
-        uint4 rb = make_uint4(0, 0, 0, 0);
-        double ul = 0.0;                       // this lane's block as a 53-bit uniform
+        // Events of this tour: kb + li (fewer than 2^32 because the step cap is
+        // at most 2^31 and every event either grows the walk or prunes a grown
+        // copy).  Lane i holds the block of event kb + i: its first word b0 and
+        // its 53-bit uniform u (exact: integers below 2^53 and power-of-two
+        // scalings).
+        uint32_t kb = 0, li = 0, b0 = 0;
+        double u = 0.0;
+        auto draw = [&]() {
+            const uint4 rb = philox10(make_uint4(kb + (uint32_t)lane, 0u, tt, s), P.key0, P.key1);
+            b0 = rb.x;
+            u = ((double)(rb.y >> 5) * 67108864.0 + (double)(rb.z >> 6)) * (1.0 / 9007199254740992.0);
+        };
+        draw();
         uint32_t n = 0;
         Key ekey = origin_key;                 // the walk's end
-        uint32_t control = 0u;                 // a decision is due at this length
+        bool control = false;                  // a decision is due at this length
+        uint32_t far_lo = ~0u;                 // first site of the walk outside its places
         // pending copies: sp entries, the one at position p in lane p mod 64
         // of the cs_* registers for p >= lo, in global memory for p < lo (at
         // most 64 in registers; the most recent ones, which are resumed first)
         uint32_t sp = 0, lo = 0;
-        XF Lc = {0.0, 0};
-        SumRec Gpre = load_const(Grow);        // pooled sum of the current length
-        // tours seen by the running average of eqn (6) (reading of Algorithm 2),
-        // converted once per tour and kept in registers
+        // tours seen by the running average of eqn (6) (reading of Algorithm 2)
+        // and its reciprocal, once per tour and kept in registers
         double seen = (double)(MGs + pool_u * (uint64_t)m);
         asm volatile("" : "+v"(seen));
+        const double seen_r = recip_normal(seen);
+
+        // The walk's weight wm * 2^we, its sum at this length Lm * 2^we and the
+        // pooled sum Gm * 2^Ge.  Inside run_ahead mantissas are left as they
+        // come (a power-of-two scale commutes with every rounding as long as
+        // nothing leaves the FP64 range) and we is constant, so a sum costs one
+        // exact shift of the other operand and the ratio none.  wm starts in
+        // [0.5, 1) and grows at most 2^6.6 per event over at most 63 events.
+        double wm, Lm, Gm;
+        int we, Ge;
+        double uf = 0.0;                       // what run_ahead compares (see arm)
+        SumRec nxt = {0.0, 0, 0u}, nxr = {0.0, 0, 0u};   // (LONG) records of the next length
+        // Makes the next events ready for run_ahead: lane i of uf holds the
+        // uniform of event kb + i, but at least 1/16 (survival at a ratio below
+        // that, which could scale wm without limit, is decided outside, as is a
+        // uniform of 0), and 2 (never below a threshold) from the event on that
+        // could end the walk, the step budget or the block, or at once while
+        // some site is outside its places.
+        auto arm = [&]() {
+            const uint32_t left = min(n_max - n, capv - c_steps);
+            uint32_t last = min(63u, li + left - 1u);
+            if (far_lo != ~0u) last = 0u;
+            const double uu = u < 0.0625 ? 0.0625 : u;
+            uf = (uint32_t)lane >= last ? 2.0 : uu;
+            if constexpr (LONG) {
+                nxt = load_global(Ls + (n + 1u + vz));
+                if constexpr (OBS) nxr = load_global(LRs + (n + 1u + vz));
+            }
+        };
+        // A walk that starts or resumes at this node decides nothing: a pooled
+        // sum just below W * seen in its place makes the ratio 1 + 2^-50, which
+        // keeps one copy (for a uniform up to 1 - 2^-50; control is false for
+        // the event loop, which sees the others).
+        auto no_decision = [&]() {
+            control = false;
+            Lm = 0.0;
+            Gm = (wm * seen) * (1.0 - 0x1p-50);
+            Ge = we;
+        };
+        auto start_at = [&](XF w) {
+            wm = w.m;
+            we = w.e + (int)vz;
+            asm volatile("" : "+v"(wm));
+        };
+        start_at(XF{0.5, 1});
+        no_decision();
+        arm();
 
         for (;;) {
-            bool bt = false;
-            // ---- the random block this step's event would draw (64 per pass) ----
-            if (k - kb >= 64u) {
-                kb = k;
-                rb = philox10(make_uint4(kb + (uint32_t)lane, 0u, tt, s), P.key0, P.key1);
-                // u of each lane's block, formed once per 64 events (exact:
-                // integers below 2^53 and power-of-two scalings)
-                ul = ((double)(rb.y >> 5) * 67108864.0 + (double)(rb.z >> 6)) * (1.0 / 9007199254740992.0);
-            }
-            const uint32_t li = k - kb;
-            const uint32_t B0 = __builtin_amdgcn_readlane(rb.x, li);
-            // pooled sums: this length's (loaded a step ago) and the next one's,
-            // which the following step uses if this one grows the walk (a step
-            // never starts at n_max, so n + 1 is inside the row)
-            const XF Gc = xf_of(Gpre);
-            const SumRec Gnx = load_const(Grow + (n + 1u));
-
-            // ---- occupancy reads of the first window, and the next length's record ----
-            // In a linear-probing run the key, if present, lies before the first
-            // empty slot, so a direction is occupied iff a window shows the key
-            // and free iff it shows an empty slot and no key.
-            const Key nk = L_::next(ekey, pdelta);
-            const uint32_t home = __umulhi(L_::hash(nk), S);
-            uint32_t slot = wrap(home + (uint32_t)poff);
-            Key v = table[slot];
-            const SumRec nxt = rec_ld(Ls + (n + 1 + vz));
-            SumRec nxr = {0.0, 0, 0u};
-            if constexpr (OBS) nxr = rec_ld(LRs + (n + 1 + vz));
-            __builtin_amdgcn_sched_barrier(0);
-
-            // ---- decision arithmetic while the reads are in flight ----
-            // eqn (6): r = W / [W_n], [W_n] = sum / seen (own epoch data weighted
-            // N in Algorithm 2), evaluated as (W * seen) / sum; only when a
-            // decision is due at this length (not after a resume or at n = 0)
-            // (computed on every step and kept only when a decision is due, so
-            // that the scan's first window resolves in the same block and its
-            // scalar work can fill the waits of this chain)
-            const XF sum = xf_add_nz(Gc, xf_mul_nz(Lc, pool));
-            uint32_t ub, fi;
-            {
-                const double r = xf_ratio_nz(xf_mul_nz(w, seen), sum);
-                const double u = lane_value(ul, li);
-                const double f = floor(r);
-                // bit 1: keep floor(r) copies (r integral, or u below
-                // ceil(r) - r); bit 3: a walk with r < 1 survives
-                ub = ufirst(((r == f || u < (f + 1.0) - r) ? 2u : 0u) | (u < r ? 8u : 0u));
-                // floor(r) as an integer: r > 0, and r <= seen / N < 2^32 because
-                // the sum includes N times the walk's own weight (the clamp
-                // only keeps the conversion defined); r >= 1 iff fi >= 1.
-                // (Converted in vector registers, then read once.)
-                uint32_t fv = (uint32_t)__builtin_fmin(f, 4294967295.0);
-                fi = ufirst(fv);
-            }
-
-            // ---- resolve the scan: usually the first window settles every direction ----
-            uint64_t freem;                    // directions resolved free
-            uint64_t insm;                     // per direction: empty lanes of the window that resolved it
-            uint32_t myslot = slot;            // this lane's slot in that window
-            {
-                const uint64_t hd = fields_any<D>(__ballot(v == nk));
-                const uint64_t empm = __ballot(v == (Key)0);
-                const uint64_t ed = fields_any<D>(empm);
-                freem = ed & ~hd;
-                insm = empm;                   // (only fields of free directions are read)
-                uint64_t pending = F::HI & ~(hd | ed);
-                // scheduling groups for this block (twenty vector instructions,
-                // then scalar and vector ones alternating one to two), which
-                // issue a step's decision and window resolution faster than the
-                // compiler's own order does
-                __builtin_amdgcn_sched_group_barrier(0x002, 20, 0);
-#pragma unroll
-                for (int g = 0; g < 16; ++g) {
-                    __builtin_amdgcn_sched_group_barrier(0x004, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-                }
-                uint32_t base = (uint32_t)poff;
-                while (pending != 0u) {
-                    // a run longer than the window: read the next W positions
-                    base += W;
-                    slot = wrap(home + base);
-                    v = table[slot];
-                    const uint64_t act = fields_lanes<D>(pending);
-                    const uint64_t hd2 = fields_any<D>(__ballot(v == nk) & act);
-                    const uint64_t emp2 = __ballot(v == (Key)0) & act;
-                    const uint64_t ed2 = fields_any<D>(emp2);
-                    const uint64_t fr = ed2 & ~hd2;
-                    freem |= fr;
-                    pending &= ~(hd2 | ed2);
-                    const uint64_t frl = fields_lanes<D>(fr);
-                    insm = (insm & ~frl) | (emp2 & frl);
-                    if ((frl >> lane) & 1u) myslot = slot;
-                }
-            }
-            // (a 32-bit count, so that its conversion to FP64 is one instruction)
-            uint32_t a = (uint32_t)__popcll(freem);
-            asm volatile("" : "+s"(a));
-            if (a == 0u) {
-                cv += (lane == ST_TRAPS) ? 1ull : 0ull;
-                bt = true;
-            } else {
-                k += 1;
-                bool pruned = false;
-                if (control) {
-                    if (fi >= 1u) {
-                        // r >= 1: c = floor(r) with probability ceil(r) - r, else ceil(r)
-                        const uint32_t ci = (ub & 2u) ? fi : fi + 1u;
-                        if (ci > 1u) {
-                            w = xf_div_nz(w, (double)ci);
-                            if (sp - lo == 64u) {
-                                // every lane holds an entry: the oldest one moves
-                                // to its place in global memory
-                                if (lane == (int)(lo & 63u)) {
-                                    StackEntry e;
-                                    e.n = cs_n;
-                                    e.remaining = cs_rem;
-                                    e.e = cs_e;
-                                    e.pad0 = 0u;
-                                    e.m = cs_m;
-                                    e.key = (uint64_t)cs_key;
-                                    store_global(stk + lo, e);
-                                }
-                                lo += 1u;
-                            }
-                            // the new entry: ci - 1 copies still to resume at (n, W / ci)
-                            const bool mine = lane == (int)(sp & 63u);
-                            cs_n = mine ? n : cs_n;
-                            cs_rem = mine ? ci - 1u : cs_rem;
-                            cs_e = mine ? w.e : cs_e;
-                            cs_m = mine ? w.m : cs_m;
-                            cs_key = mine ? ekey : cs_key;
-                            sp += 1;
-                            c_maxd = (sp > c_maxd) ? sp : c_maxd;
-                            cv += (lane == ST_ENRICH) ? 1ull
-                                  : ((lane == ST_COPIES) ? (uint64_t)(ci - 1u) : 0ull);
-                        }
-                    } else if (ub & 8u) {
-                        w = xf_div_nz(sum, seen);  // r < 1, survives: W / r
+            // ---- run ahead: common events, until one is not ----
+            // (what the event that stopped it needs is left in these)
+            Key nk;
+            uint32_t slot, a, x, ra = rec_base + n * 16u + vz, sa = sid_base + n * 2u + vz;
+            uint64_t hits;
+            Key v;
+            SumRec Gn;
+            uint32_t il;
+            const uint32_t li0 = li;
+            auto run_ahead = [&](auto decide) {
+                for (;;) {
+                    // occupancy reads, the next length's record and pooled sum
+                    nk = S_::next(ekey, pdelta);
+                    slot = slot_of(nk);
+                    v = lds_load<Key>(slot * (uint32_t)sizeof(Key) + lds_address(table));
+                    SumRec nx2 = {0.0, 0, 0u}, nr2 = {0.0, 0, 0u};
+                    if constexpr (LONG) {
+                        // (one length further: it has a whole step to arrive.  At
+                        // n_max - 1 that is past the last record: row is padded to
+                        // 16 records or the next array follows; never used)
+                        nx2 = load_global(reinterpret_cast<const SumRec*>(
+                            reinterpret_cast<const unsigned char*>(Ls) + ra) + 2);
+                        if constexpr (OBS)
+                            nr2 = load_global(reinterpret_cast<const SumRec*>(
+                                reinterpret_cast<const unsigned char*>(LRs) + ra) + 2);
                     } else {
-                        pruned = true;             // r < 1, pruned with probability 1 - r
+                        nxt = record_of(lds_load<u32x4>(ra + 16u));
+                        if constexpr (OBS) nxr = record_of(lds_load<u32x4>(ra + 16u + row_lds));
                     }
-                }
-                if (pruned) {
-                    cv += (lane == ST_PRUNES) ? 1ull : 0ull;
-                    bt = true;
-                } else {
-                    // ---- Rosenbluth growth: the j-th free neighbour ----
-                    // (the free direction whose field-top lane has exactly j
-                    // free field tops below it)
+                    Gn = pooled(ra + 16u);
+                    const uint32_t B0 = lane_value(b0, li);
+                    const double uu = lane_value(uf, li);
+                    // the next length's sum at this scale; the term that adds it
+                    // to u is below its last place unless the sum is 2^440 times
+                    // the weight or more, which stops here
+                    const double t = ldexp(nxt.m, nxt.e - we);
+                    const double ut = __builtin_fma(t, 0x1p-501, uu);
+                    double w1 = wm;
+                    uint64_t ok;
+                    if constexpr (decltype(decide)::value) {
+                        // eqn (6): r = W / [W_n], [W_n] = sum / seen (own epoch
+                        // data weighted N in Algorithm 2), as (W * seen) / sum.
+                        // One copy goes on iff u < r < 1 (a survivor, which takes
+                        // sum / seen) or 1 <= r < 2 and u < 2 - r.
+                        const double sum = ldexp(Gm, Ge - we) + Lm * pool;
+                        const double r = div_by(wm * seen, sum, recip_normal(sum));
+                        ok = __ballot(ut < min_f64(r, 2.0 - r));
+                        const double ws = div_by(sum, seen, seen_r);
+                        w1 = r < 1.0 ? ws : wm;
+                    } else {
+                        ok = __ballot(ut < 1.0);
+                    }
+                    hits = __ballot(v == nk);
+                    a = (uint32_t)(2 * D) - mask_count(hits);
+                    // The j-th free neighbour, j = floor(B0 a / 2^32): the number
+                    // of free directions below a lane's own is pdir less the hits
+                    // in lanes below it, so x is 0 in the chosen direction's
+                    // lanes (and in lanes of occupied neighbours of it: those up
+                    // to the hit, which are not empty, before it, those past the
+                    // hit after it).  Its first empty place is the lowest lane
+                    // with x = 0 that read an empty slot.
                     const uint32_t j = __umulhi(B0, a);
-                    const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                        (uint32_t)(freem >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)freem, 0u));
-                    const uint64_t pick = __ballot(below == j) & freem;
-                    const int dir = (__ffsll((unsigned long long)pick) - 1) >> F::LW;
-                    digest = (digest ^ ((uint32_t)dir | (a << 3))) * FNV_PRIME;
-                    // insertion slot: the first empty slot of the chosen direction's run
-                    const uint32_t il =
-                        (uint32_t)__builtin_ctz((uint32_t)(insm >> (dir * W)) & FIELD) + (uint32_t)(dir * W);
-                    const uint32_t ins_slot = __builtin_amdgcn_readlane(myslot, il);
+                    x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j - (uint32_t)pdir));
+                    const uint64_t pick = __ballot((x | S_::mark(v)) == 0u) & ok;
+                    if (pick == 0ull) break;             // also where no neighbour is free
+                    il = (uint32_t)__builtin_ctzll(pick);
+                    if ((BLANK >> il) & 1ull) break;     // all places taken
+                    // grow: W *= a_+, eqn (2), and record, eqn (4)
+                    wm = w1 * (double)a;
+                    Lm = t + wm;
+                    write_arrival<LONG>(il, slot * (uint32_t)sizeof(Key) + lds_address(table), nk, sa, slot, ra,
+                                        words_of(Lm, we, nxt.h + 1u), Ls);
                     ekey = lane_value(nk, il);
-                    // W *= a_+, eqn (2).  No range check is needed here: |e|
-                    // grows by at most 3 per step and falls by at most 33 per
-                    // decision, so it stays below 2^21 for every n_max allowed.
-                    w = xf_mul_nz(w, (double)a);
-                    n += 1;
-                    c_steps += 1;
-                    Gpre = Gnx;
-                    // (moved to vector registers here, before the LDS writes below,
-                    // so that waiting for its scalar load never waits for them)
-                    asm volatile("" : "+v"(Gpre.m), "+v"(Gpre.e));
-                    // ---- arrival: record into the running sums, eqn (4) ----
-                    // (formed before the table insert, so that waiting for the
-                    // record read never waits for the insert's LDS writes too)
-                    const XF Lnew = xf_add_nz(xf_of(nxt), w);
-                    SumRec nr;
-                    nr.m = Lnew.m;
-                    nr.e = Lnew.e;
-                    nr.h = nxt.h + 1u;
-                    if (lane == 0) {
-                        table[ins_slot] = ekey;
-                        sid[n] = (uint16_t)ins_slot;
-                        rec_st(Ls + n, nr);
-                    }
-                    Lc = Lnew;
                     if constexpr (OBS) {
                         // R^2 of the new end, exact in FP64 (|coordinates| < 2^15)
-                        int x, y, z;
-                        L_::unpack(ekey, x, y, z);
-                        const double r2 = (double)x * (double)x + (double)y * (double)y +
-                                          (double)z * (double)z;
-                        const XF R = xf_add_nz(xf_of(nxr), xf_mul_nz(w, r2));
+                        int cx, cy, cz;
+                        S_::unpack(ekey, cx, cy, cz);
+                        const double r2 = (double)cx * (double)cx + (double)cy * (double)cy +
+                                          (double)cz * (double)cz;
                         SumRec rr;
-                        rr.m = R.m;
-                        rr.e = R.e;
+                        rr.m = ldexp(nxr.m, nxr.e - we) + wm * r2;
+                        rr.e = we;
                         rr.h = 0u;
-                        if (lane == 0) rec_st(LRs + n, rr);
+                        if (lane == 0) {
+                            if constexpr (LONG)
+                                store_global(reinterpret_cast<SumRec*>(reinterpret_cast<unsigned char*>(LRs) + ra) + 1,
+                                             rr);
+                            else
+                                *reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds + (ra - rec_base) + 16u) = rr;
+                        }
                     }
-                    if (c_steps >= capv) {
-                        abort = true;
-                        break;
+                    digest = (digest ^ ((il >> LW) | (a << 3))) * FNV_PRIME;
+                    Gm = Gn.m;
+                    Ge = Gn.e;
+                    ra += 16u;
+                    sa += 2u;
+                    li += 1u;
+                    if constexpr (LONG) {
+                        nxt = nx2;
+                        if constexpr (OBS) nxr = nr2;
                     }
-                    if (n == n_max) bt = true;
-                    else control = control_mode;
                 }
+            };
+            if (control_mode) run_ahead(yes{});
+            else run_ahead(no{});
+            n += li - li0;
+            c_steps += li - li0;
+            control = (li != li0) ? control_mode : control;
+
+            // ---- the event that stopped it ----
+            uint64_t outside = 0ull;           // directions found outside their places (last lanes)
+            if (far_lo != ~0u) {
+                for (uint32_t b = far_lo; b <= n; b += 64u) {
+                    const uint32_t i = b + (uint32_t)lane;
+                    const Key k = i <= n ? table[sid[i]] : (Key)0;
+#pragma unroll
+                    for (int d = 0; d < 2 * D; ++d)
+                        if (__ballot(k == lane_value(nk, d * W)) != 0ull && ((hits >> (d * W)) & FIELD) == 0ull)
+                            outside |= 1ull << (d * W + W - 1);
+                }
+            }
+            const uint32_t au = (uint32_t)(2 * D) - (uint32_t)__popcll(hits | outside);
+            bool bt = false, pruned = false;
+            XF w = xf_norm_nz(wm, we);
+            if (au == 0u) {
+                cv += (lane == ST_TRAPS) ? 1ull : 0ull;
+                bt = true;
+            } else if (control) {
+                // the decision in full
+                const SumRec here = rec_ld(Ls + (n + vz));
+                const XF sum = xf_add_nz(XF{Gm, Ge}, xf_mul_nz(xf_norm_nz(here.m, here.e), pool));
+                const double r = xf_ratio_nz(xf_mul_nz(w, seen), sum);
+                const double ul = lane_value(u, li);
+                const double f = floor(r);
+                // floor(r) as an integer: r > 0, and r <= seen / N < 2^32 because
+                // the sum includes N times the walk's own weight (the clamp
+                // only keeps the conversion defined); r >= 1 iff fi >= 1
+                const uint32_t fi = ufirst((uint32_t)__builtin_fmin(f, 4294967295.0));
+                if (fi >= 1u) {
+                    // r >= 1: c = floor(r) with probability ceil(r) - r, else ceil(r)
+                    // (r integral: u < 1)
+                    const uint32_t ci = ubool(ul < (f + 1.0) - r) ? fi : fi + 1u;
+                    if (ci > 1u) {
+                        w = xf_div_nz(w, (double)ci);
+                        if (sp - lo == 64u) {
+                            // every lane holds an entry: the oldest one moves
+                            // to its place in global memory
+                            if (lane == (int)(lo & 63u)) {
+                                StackEntry e;
+                                e.n = cs_n;
+                                e.remaining = cs_rem;
+                                e.e = cs_e;
+                                e.pad0 = 0u;
+                                e.m = cs_m;
+                                e.key = (uint64_t)cs_key;
+                                store_global(stk + lo, e);
+                            }
+                            lo += 1u;
+                        }
+                        // the new entry: ci - 1 copies still to resume at (n, W / ci)
+                        const bool mine = lane == (int)(sp & 63u);
+                        cs_n = mine ? n : cs_n;
+                        cs_rem = mine ? ci - 1u : cs_rem;
+                        cs_e = mine ? w.e : cs_e;
+                        cs_m = mine ? w.m : cs_m;
+                        cs_key = mine ? ekey : cs_key;
+                        sp += 1;
+                        c_maxd = (sp > c_maxd) ? sp : c_maxd;
+                        cv += (lane == ST_ENRICH) ? 1ull
+                              : ((lane == ST_COPIES) ? (uint64_t)(ci - 1u) : 0ull);
+                    }
+                } else if (ubool(ul < r)) {
+                    w = xf_div_nz(sum, seen);  // r < 1, survives: W / r
+                } else {
+                    pruned = true;             // r < 1, pruned with probability 1 - r
+                }
+            }
+            if (pruned) {
+                cv += (lane == ST_PRUNES) ? 1ull : 0ull;
+                li += 1u;
+                bt = true;
+            } else if (!bt) {
+                // ---- growth, as above, with every case of the sums and the table ----
+                if (far_lo != ~0u) {
+                    const uint64_t occ = hits | outside;
+                    const uint32_t j = __umulhi(lane_value(b0, li), au);
+                    x = __builtin_amdgcn_mbcnt_hi((uint32_t)(occ >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)occ, j - (uint32_t)pdir));
+                }
+                il = (uint32_t)__builtin_ctzll(__ballot((x | S_::mark(v)) == 0u) & ~outside);
+                ekey = lane_value(nk, il);
+                uint32_t ins = lane_value(slot, il);
+                if ((BLANK >> il) & 1ull) {
+                    // all places taken: the first empty slot of the table
+                    // (slots outnumber the sites of the longest walk)
+                    for (uint32_t b = 0;; b += 64u) {
+                        const uint32_t i = b + (uint32_t)lane;
+                        const uint64_t em =
+                            __ballot(i < sub * (uint32_t)(W - 1) && S_::empty(table[min(i, S - 1u)]));
+                        if (em != 0ull) {
+                            ins = b + (uint32_t)__builtin_ctzll(em);
+                            break;
+                        }
+                    }
+                    far_lo = min(far_lo, n + 1u);
+                }
+                digest = (digest ^ ((il >> LW) | (au << 3))) * FNV_PRIME;
+                w = xf_mul_nz(w, (double)au);
+                n += 1u;
+                c_steps += 1u;
+                const XF Lnew = xf_add_nz(xf_of(nxt), w);
+                SumRec nr;
+                nr.m = Lnew.m;
+                nr.e = Lnew.e;
+                nr.h = nxt.h + 1u;
+                if (lane == 0) {
+                    table[ins] = ekey;
+                    sid[n] = (uint16_t)ins;
+                    rec_st(Ls + n, nr);
+                }
+                if constexpr (OBS) {
+                    int cx, cy, cz;
+                    S_::unpack(ekey, cx, cy, cz);
+                    const double r2 = (double)cx * (double)cx + (double)cy * (double)cy + (double)cz * (double)cz;
+                    const XF R = xf_add_nz(xf_of(nxr), xf_mul_nz(w, r2));
+                    SumRec rr;
+                    rr.m = R.m;
+                    rr.e = R.e;
+                    rr.h = 0u;
+                    if (lane == 0) rec_st(LRs + n, rr);
+                }
+                wave_fence();
+                li += 1u;
+                if (c_steps >= capv) {
+                    abort = true;
+                    break;
+                }
+                // (a sum out of this weight's range makes the ratio 0 or no
+                // number, and the decision is made here)
+                start_at(w);
+                Lm = ldexp(Lnew.m, Lnew.e - we);
+                Gm = Gn.m;
+                Ge = Gn.e;
+                control = control_mode;
+                bt = n == n_max;
             }
             if (bt) {
                 // ---- resume the most recent pending copy, or end the tour ----
@@ -1126,31 +1340,46 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
                 const uint32_t tl = (sp - 1u) & 63u;
                 const uint32_t rn = lane_value(cs_n, tl);
                 const uint32_t rem = lane_value(cs_rem, tl);
-                w = XF{lane_value(cs_m, tl), (int32_t)lane_value((uint32_t)cs_e, tl)};
+                start_at(XF{lane_value(cs_m, tl), (int32_t)lane_value((uint32_t)cs_e, tl)});
                 ekey = (Key)lane_value(cs_key, tl);
                 if (rem == 1u) sp -= 1u;       // its last copy: the entry is done
                 else cs_rem -= (lane == (int)tl) ? 1u : 0u;
                 // LIFO deletion of sites rn+1..n restores the table exactly
                 for (uint32_t i = rn + 1u + (uint32_t)lane; i <= n; i += 64u) table[sid[i]] = (Key)0;
                 n = rn;
-                control = 0u;
+                if (far_lo > n) far_lo = ~0u;
+                no_decision();
                 wave_fence();
             }
+            if (li == 64u) {
+                kb += 64u;
+                li = 0u;
+                draw();
+            }
+            arm();
         }
         // end of the tour (or abort): back to the empty walk
-        c_events += k;
+        c_events += kb + li;
         for (uint32_t i = 1u + (uint32_t)lane; i <= n; i += 64u) table[sid[i]] = (Key)0;
         wave_fence();
     }
     cv += (lane == ST_EVENTS) ? c_events : 0ull;
+    // the sums leave normalised (m in [0.5, 1), or 0 with e = 0)
+    auto leave = [&](SumRec* p, SumRec* out) {
+        SumRec r = rec_ld(p);
+        const XF v = xf_norm(r.m, r.e);
+        r.m = v.m;
+        r.e = v.e;
+        if constexpr (!LONG) *p = r;
+        store_global(out, r);
+    };
     if (lane == 0) rec_st(Ls, rec0);
     wave_fence();
-    if constexpr (!LONG) {
-        for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) store_global(Lrow + i, Ls[i]);
-        if constexpr (OBS) {
-            for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) store_global(P.LR + rb0 + i, LRs[i]);
-        }
+    for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) {
+        leave(Ls + i, Lrow + i);
+        if constexpr (OBS) leave(LRs + i, P.LR + rb0 + i);
     }
+    wave_fence();
     if (lane == 0) {
         if (abort) atomicOr(&P.ctrl[CTRL_ERR], ERR_CAP);
         uint64_t* sr = P.stats + (size_t)s * STATS_WORDS;
