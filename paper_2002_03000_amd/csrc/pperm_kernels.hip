@@ -208,6 +208,10 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Every lambda of the walker belongs in its caller: one left as a call would
+// keep what it captures in memory.
+#define INLINE __attribute__((always_inline))
+
 // Compile-time switches of a generic lambda.
 struct yes { static constexpr bool value = true; };
 struct no { static constexpr bool value = false; };
@@ -819,6 +823,31 @@ __device__ __forceinline__ void write_arrival(uint32_t il, uint32_t taddr, uint6
                      : "memory", "scc");
 }
 
+// The lowest bit set in m, or all ones for none.
+__device__ __forceinline__ uint32_t first_bit(uint64_t m) {
+    uint32_t r;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(r) : "s"(m));
+    return r;
+}
+
+// Empties the slots at LDS addresses `at` of the lanes whose `index` is below
+// `depth` (a vector compare that selects the lanes itself: through a saved mask
+// the scalar unit would wait for it).
+template <typename Key>
+__device__ __forceinline__ void clear_sites(uint32_t index, uint32_t depth, uint32_t at) {
+    const Key zero = 0;
+    if constexpr (sizeof(Key) == 8)
+        asm volatile("v_cmpx_lt_u32_e32 %0, %1\n\t"
+                     "ds_write_b64 %2, %3\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "v"(index), "v"(depth), "v"(at), "v"(zero) : "memory", "vcc");
+    else
+        asm volatile("v_cmpx_lt_u32_e32 %0, %1\n\t"
+                     "ds_write_b32 %2, %3\n\t"
+                     "s_mov_b64 exec, -1"
+                     :: "v"(index), "v"(depth), "v"(at), "v"(zero) : "memory", "vcc");
+}
+
 // One sequence's `tours` tours against frozen pooled sums (the whole hot path
 // of one walk); run by one wavefront.  Gsrc: the pooled sums to read (the
 // problem's own, or an epoch's copy in a chained launch); fresh: the epoch
@@ -837,28 +866,30 @@ __device__ __forceinline__ void write_arrival(uint32_t il, uint32_t taddr, uint6
 // for a branch not taken, 20 for one taken, 16 where the scalar unit reads what
 // the vector unit wrote.  So the common event -- a walk with a free neighbour,
 // a decision that keeps one copy (or a survivor), a growth that ends neither
-// the walk, the random block nor the step budget -- is one straight block of
-// vector code with a single loop branch (run_ahead), and everything else is
-// found by that block's one test and handled outside it (see the event loop).
-// Before, with every case decided in line (255 instructions and 17 branches a
-// step): one square sequence of 20-step walks, 1000 tours, 12.36 ms, now 8.42;
-// 4096 square sequences of 500 steps, 64 tours, 94.7 ms, now 70.2; 16384 cubic
-// ones of 1000 steps, 32 tours, 205 ms, now 149; 256 Rosenbluth walks of up to
-// 6000 cubic steps, twice, 6.40 ms, now 3.40.
+// the walk, the random block nor the step budget -- is one straight block of 78
+// instructions, mostly vector code, with a single branch, its own loop's
+// (run_ahead); enrichment to two copies, pruning and trapping (a quarter of the
+// square lattice's events) are short blocks beside it; and everything else is
+// handled outside, in the extended-range form (the event loop).
+// Measured (ms): with every case decided in line, 255 instructions and 17
+// branches a step / the straight block alone / with the blocks beside it:
+//   one square sequence of 20-step walks, 1000 tours       12.46 / 8.42 / 6.72
+//   4096 square sequences of 500 steps, 64 tours            94.6 / 70.2 / 47.6
+//   16384 cubic sequences of 1000 steps, 32 tours            198 /  149 /  101
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice   6.41 / 3.40 / 2.15
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 
 template <int D, bool OBS = false, bool LONG = false, bool CK = false>
-__device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t tours, uint32_t cap,
+__device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint32_t tours, uint32_t cap,
                                                   uint32_t s, unsigned char* lds, const SumRec* Gsrc,
                                                   bool fresh) {
+    const ProblemDesc P = load_const(desc);
     static_assert(!(OBS && CK), "observables need coordinates, which compact keys do not keep");
     using S_ = typename SiteOf<D, CK>::T;
     using Key = typename S_::Key;
     constexpr int W = (D == 2) ? 16 : 8;       // lanes per direction
     constexpr int LW = (D == 2) ? 4 : 3;
     constexpr uint64_t FIELD = (1ull << W) - 1ull;
-    // the last lane of every direction
-    constexpr uint64_t BLANK = (D == 2) ? 0x8000800080008000ull : 0x0000808080808080ull;
 
     // LDS: the occupancy table, the slot id of every site of the walk and the
     // sequence's own per-length sums (moved in at the start of the sequence's
@@ -871,11 +902,11 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     SumRec* LRs = LONG ? P.LR + (size_t)s * P.row
                        : reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds);
     // record access: LDS, or the global row of a long walk
-    auto rec_ld = [&](const SumRec* p) -> SumRec {
+    auto rec_ld = [&](const SumRec* p) INLINE -> SumRec {
         if constexpr (LONG) return load_global(p);
         else return *p;
     };
-    auto rec_st = [&](SumRec* p, const SumRec& v) {
+    auto rec_st = [&](SumRec* p, const SumRec& v) INLINE {
         if constexpr (LONG) store_global(p, v);
         else *p = v;
     };
@@ -905,7 +936,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     const uint32_t lane_base = blank ? S - 1u : (uint32_t)poff * sub;
     const uint32_t lane_mul = ((0x9E3779B1u * (uint32_t)(poff + 1)) ^ (0x85EBCA77u * (uint32_t)(poff + 3))) | 1u;
     const Key pdelta = S_::delta(pdir);
-    auto slot_of = [&](Key k) { return __umulhi(S_::word(k) * lane_mul, lane_sub) + lane_base; };
+    auto slot_of = [&](Key k) INLINE { return __umulhi(S_::word(k) * lane_mul, lane_sub) + lane_base; };
 
     // A zero the compiler cannot see through: addresses and sums formed with it
     // stay in vector registers.
@@ -938,8 +969,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     SumRec* __restrict__ Lrow = P.L + rb0;
     const SumRec* Grow = shared_mode ? Gsrc : Gsrc + rb0;
     if (!shared_mode) MGs = ufirst64(P.MG[s]);
-    const uint64_t t0 = ufirst64(P.t[s]);
-    uint32_t tlo = (uint32_t)t0;               // tour index: its low word keys the random numbers
+    uint32_t tlo = ufirst((uint32_t)P.t[s]);               // tour index: its low word keys the random numbers
     uint32_t m = fresh ? 0u : ufirst(P.m[s]);
     if constexpr (!LONG) {
         if (fresh) {
@@ -961,17 +991,16 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     }
     wave_fence();
     SumRec rec0 = rec_ld(Ls);
-    // counters of this call, added to the sequence's totals at its end: the
-    // step count (scalar, it drives the cap) and one counter per lane of `cv`
-    // (lane i accumulates statistics word i)
-    uint32_t c_steps = 0, c_tours = 0, c_maxd = 0;
+    // counters of this call, added to the sequence's totals at its end
+    // (every event grows the walk or prunes a copy, so the steps are the events
+    // less the prunings)
+    uint32_t c_tours = 0, c_maxd = 0, c_enrich = 0, c_prunes = 0, c_traps = 0;
+    uint64_t c_copies = 0, c_events = 0;
     const uint32_t capv = cap ? cap : 0xFFFFFFFFu;   // step cap of this call (0: none)
-    uint64_t c_events = 0;                     // events: the sum over tours of kb + li
-    uint64_t cv = 0;
     uint32_t digest = (uint32_t)P.stats[(size_t)s * STATS_WORDS + ST_DIGEST] + vz;
     bool abort = false;
     // the registers of the copy stack (see the tour loop)
-    uint32_t cs_n = 0u, cs_rem = 0u;
+    uint32_t cs_ra = 0u, cs_rem = 0u;
     int32_t cs_e = 0;
     double cs_m = 0.0;
     Key cs_key = (Key)0;
@@ -982,9 +1011,14 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     const uint32_t rec_base = LONG ? 0u : lds_address(Ls);
     const uint32_t sid_base = lds_address(sid);
     const unsigned char* gsums = reinterpret_cast<const unsigned char*>(Grow) - rec_base;
-    auto pooled = [&](uint32_t address) {
+    auto pooled = [&](uint32_t address) INLINE {
         return load_global(reinterpret_cast<const SumRec*>(gsums + address));
     };
+
+    // 2^-501 in a register (see run_ahead), and twice the lane
+    double small = 0x1p-501;
+    asm volatile("" : "+v"(small));
+    const uint32_t lane2 = 2u * (uint32_t)lane;
 
     for (uint32_t tour = 0; tour < tours && !abort; ++tour) {
         // ---- a pass through the empty walk (eqn (4), M) ----
@@ -998,22 +1032,28 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
             rec0.e = r0.e;
             rec0.h += 1u;
         }
-        // Events of this tour: kb + li (fewer than 2^32 because the step cap is
-        // at most 2^31 and every event either grows the walk or prunes a grown
-        // copy).  Lane i holds the block of event kb + i: its first word b0 and
-        // its 53-bit uniform u (exact: integers below 2^53 and power-of-two
-        // scalings).
-        uint32_t kb = 0, li = 0, b0 = 0;
+        // Events of this tour: kb + li - 1 so far (fewer than 2^32 because the
+        // step cap is at most 2^31 and every event either grows the walk or
+        // prunes a grown copy).  Lane i of 1 .. 63 holds the random block of
+        // event kb + i - 1: its first word b0 and its 53-bit uniform u (exact:
+        // integers below 2^53 and power-of-two scalings).  Event 64 of a block
+        // reads lane 0, which stops run_ahead.
+        uint32_t kb = 0, li = 1, b0 = 0;
         double u = 0.0;
-        auto draw = [&]() {
-            const uint4 rb = philox10(make_uint4(kb + (uint32_t)lane, 0u, tt, s), P.key0, P.key1);
+        auto draw = [&]() INLINE {
+            // (the key schedule is formed here each time: hoisted, it would take
+            // twenty scalar registers)
+            uint32_t k0 = P.key0, k1 = P.key1;
+            asm volatile("" : "+s"(k0), "+s"(k1));
+            const uint4 rb = philox10(make_uint4(kb + (uint32_t)lane - 1u, 0u, tt, s), k0, k1);
             b0 = rb.x;
             u = ((double)(rb.y >> 5) * 67108864.0 + (double)(rb.z >> 6)) * (1.0 / 9007199254740992.0);
         };
         draw();
-        uint32_t n = 0;
+        // the walk's length, as the addresses of its record and of its slot id
+        uint32_t ra = rec_base + vz, sa = sid_base + vz;
+        auto length = [&]() INLINE { return (ufirst(ra) - rec_base) >> 4; };
         Key ekey = origin_key;                 // the walk's end
-        bool control = false;                  // a decision is due at this length
         uint32_t far_lo = ~0u;                 // first site of the walk outside its places
         // pending copies: sp entries, the one at position p in lane p mod 64
         // of the cs_* registers for p >= lo, in global memory for p < lo (at
@@ -1029,295 +1069,367 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
         // pooled sum Gm * 2^Ge.  Inside run_ahead mantissas are left as they
         // come (a power-of-two scale commutes with every rounding as long as
         // nothing leaves the FP64 range) and we is constant, so a sum costs one
-        // exact shift of the other operand and the ratio none.  wm starts in
-        // [0.5, 1) and grows at most 2^6.6 per event over at most 63 events.
+        // exact shift of the other operand and the ratio none.  wm is in
+        // [0.5, 1) when a block of events begins or a copy resumes; one event
+        // at most halves it or makes it 2^6.6 times larger.
         double wm, Lm, Gm;
         int we, Ge;
         double uf = 0.0;                       // what run_ahead compares (see arm)
-        SumRec nxt = {0.0, 0, 0u}, nxr = {0.0, 0, 0u};   // (LONG) records of the next length
+        uint32_t last = 0;                     // the event that stops it whatever it is
+        SumRec nxt = {0.0, 0, 0u}, nxr = {0.0, 0, 0u};   // records of the next length
+        auto steps = [&]() INLINE { return (uint32_t)c_events + kb + li - 1u - c_prunes; };
         // Makes the next events ready for run_ahead: lane i of uf holds the
-        // uniform of event kb + i, but at least 1/16 (survival at a ratio below
+        // uniform of its event, but at least 1/16 (survival at a ratio below
         // that, which could scale wm without limit, is decided outside, as is a
         // uniform of 0), and 2 (never below a threshold) from the event on that
-        // could end the walk, the step budget or the block, or at once while
-        // some site is outside its places.
-        auto arm = [&]() {
-            const uint32_t left = min(n_max - n, capv - c_steps);
-            uint32_t last = min(63u, li + left - 1u);
-            if (far_lo != ~0u) last = 0u;
+        // could end the walk or the step budget, or at once while some site is
+        // outside its places.  (After a resume the walk's end is further off
+        // than this says, which only stops run_ahead for nothing.)
+        auto arm = [&](uint32_t n) INLINE {
+            const uint32_t left = min(n_max - n, capv - steps());
+            last = far_lo != ~0u ? li : min(64u, li + left - 1u);
             const double uu = u < 0.0625 ? 0.0625 : u;
-            uf = (uint32_t)lane >= last ? 2.0 : uu;
+            uf = ((uint32_t)lane >= last || lane == 0) ? 2.0 : uu;
+        };
+        // (LONG) the next length's records, from global memory
+        auto load_next = [&]() INLINE {
             if constexpr (LONG) {
-                nxt = load_global(Ls + (n + 1u + vz));
-                if constexpr (OBS) nxr = load_global(LRs + (n + 1u + vz));
+                nxt = load_global(reinterpret_cast<const SumRec*>(reinterpret_cast<const unsigned char*>(Ls) + ra) + 1);
+                if constexpr (OBS)
+                    nxr = load_global(
+                        reinterpret_cast<const SumRec*>(reinterpret_cast<const unsigned char*>(LRs) + ra) + 1);
             }
         };
-        // A walk that starts or resumes at this node decides nothing: a pooled
-        // sum just below W * seen in its place makes the ratio 1 + 2^-50, which
-        // keeps one copy (for a uniform up to 1 - 2^-50; control is false for
-        // the event loop, which sees the others).
-        auto no_decision = [&]() {
-            control = false;
+        // A walk that starts or resumes decides nothing at its length: a pooled
+        // sum of exactly W * seen and no sum of its own make the ratio exactly
+        // 1, which keeps one copy (and no sum, Lm = 0, marks the case).
+        auto no_decision = [&]() INLINE {
             Lm = 0.0;
-            Gm = (wm * seen) * (1.0 - 0x1p-50);
+            Gm = wm * seen;
             Ge = we;
         };
-        auto start_at = [&](XF w) {
+        auto weigh = [&](XF w) INLINE {
             wm = w.m;
             we = w.e + (int)vz;
             asm volatile("" : "+v"(wm));
         };
-        start_at(XF{0.5, 1});
+        weigh(XF{0.5, 1});
         no_decision();
-        arm();
+        load_next();
+        arm(0u);
+
+        // what scan leaves: the neighbours' keys, slots and contents, the hits,
+        // a_+, the choice, and the decision
+        Key nk, v;
+        uint32_t slot, a, x, il;
+        uint64_t hits, pick;
+        double t, ut, uu, r = 0.0, w1;
+        SumRec Gn, nx2 = {0.0, 0, 0u}, nr2 = {0.0, 0, 0u};
+        auto scan = [&](auto decide) INLINE {
+            // occupancy reads, the next length's record and pooled sum
+            nk = S_::next(ekey, pdelta);
+            slot = slot_of(nk);
+            v = lds_load<Key>(slot * (uint32_t)sizeof(Key) + lds_address(table));
+            if constexpr (LONG) {
+                // (one length further: it has a whole step to arrive.  At
+                // n_max - 1 that is past the last record: row is padded to
+                // 16 records or the next array follows; never used)
+                nx2 = load_global(reinterpret_cast<const SumRec*>(reinterpret_cast<const unsigned char*>(Ls) + ra) + 2);
+                if constexpr (OBS)
+                    nr2 = load_global(
+                        reinterpret_cast<const SumRec*>(reinterpret_cast<const unsigned char*>(LRs) + ra) + 2);
+            } else {
+                nxt = record_of(lds_load<u32x4>(ra + 16u));
+                if constexpr (OBS) nxr = record_of(lds_load<u32x4>(ra + 16u + row_lds));
+            }
+            uu = lane_value(uf, li);
+            double thr = 1.0;
+            w1 = wm;
+            if constexpr (decltype(decide)::value) {
+                // eqn (6): r = W / [W_n], [W_n] = sum / seen (own epoch
+                // data weighted N in Algorithm 2), as (W * seen) / sum.
+                // One copy goes on iff u < r < 1 (a survivor, which takes
+                // sum / seen) or 1 <= r < 2 and u < 2 - r.
+                const double sum = ldexp(Gm, Ge - we) + Lm * pool;
+                r = div_by(wm * seen, sum, recip_normal(sum));
+                thr = min_f64(r, 2.0 - r);
+                const double ws = div_by(sum, seen, seen_r);
+                w1 = r < 1.0 ? ws : wm;
+                Gn = pooled(ra + 16u);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            hits = __ballot(v == nk);
+            a = (uint32_t)(2 * D) - mask_count(hits);
+            // The j-th free neighbour, j = floor(B0 a / 2^32): the number
+            // of free directions below a lane's own is pdir less the hits
+            // in lanes below it, so x is 0 in the chosen direction's
+            // lanes (and in lanes of occupied neighbours of it: those up
+            // to the hit, which are not empty, before it, those past the
+            // hit after it).  Its first empty place is the lowest lane
+            // with x = 0 that read an empty slot.
+            const uint32_t j = __umulhi(lane_value(b0, li), a);
+            x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j - (uint32_t)pdir));
+            pick = __ballot((x | S_::mark(v)) == 0u);
+            // the next length's sum at this scale; the term that adds it
+            // to u is below its last place unless the sum is 2^440 times
+            // the weight or more, which stops here
+            t = ldexp(nxt.m, nxt.e - we);
+            ut = __builtin_fma(t, small, uu);
+            il = first_bit(pick & __ballot(ut < thr));
+        };
+        // (il is all ones where nothing was chosen, and a last lane where all
+        // places of the chosen neighbour are taken)
+        auto chosen = [&]() INLINE { return (~il & (uint32_t)(W - 1)) != 0u; };
+        // growth by the lane `il`: W *= a_+, eqn (2), and the record, eqn (4)
+        auto commit = [&](double w) INLINE {
+            wm = w * (double)a;
+            Lm = t + wm;
+            write_arrival<LONG>(il, slot * (uint32_t)sizeof(Key) + lds_address(table), nk, sa, slot, ra,
+                                words_of(Lm, we, nxt.h + 1u), Ls);
+            ekey = lane_value(nk, il);
+            if constexpr (OBS) {
+                // R^2 of the new end, exact in FP64 (|coordinates| < 2^15)
+                int cx, cy, cz;
+                S_::unpack(ekey, cx, cy, cz);
+                const double r2 = (double)cx * (double)cx + (double)cy * (double)cy + (double)cz * (double)cz;
+                SumRec rr;
+                rr.m = ldexp(nxr.m, nxr.e - we) + wm * r2;
+                rr.e = we;
+                rr.h = 0u;
+                if (lane == 0) {
+                    if constexpr (LONG)
+                        store_global(reinterpret_cast<SumRec*>(reinterpret_cast<unsigned char*>(LRs) + ra) + 1, rr);
+                    else
+                        *reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds + (ra - rec_base) + 16u) = rr;
+                }
+            }
+            digest = (digest ^ ((il >> LW) | (a << 3))) * FNV_PRIME;
+            Gm = Gn.m;
+            Ge = Gn.e;
+            ra += 16u;
+            sa += 2u;
+            li += 1u;
+            if constexpr (LONG) {
+                nxt = nx2;
+                if constexpr (OBS) nxr = nr2;
+            }
+        };
+        // a copy stack entry: `copies` still to resume here with weight w
+        auto push = [&](double w, uint32_t copies) INLINE {
+            const bool mine = lane == (int)(sp & 63u);
+            cs_ra = mine ? ra : cs_ra;
+            cs_rem = mine ? copies : cs_rem;
+            cs_e = mine ? we : cs_e;
+            cs_m = mine ? w : cs_m;
+            cs_key = mine ? ekey : cs_key;
+            sp += 1u;
+            c_maxd = max(c_maxd, sp);
+            c_enrich += 1u;
+            c_copies += (uint64_t)copies;
+        };
+        // back to the most recent pending copy, which the registers hold
+        auto resume = [&]() INLINE {
+            // (the slot ids of the last 64 sites; a short walk's reach into the
+            // table before them and are not used)
+            uint32_t at = lds_load<uint16_t>(sa - lane2);
+            const uint32_t tl = (sp - 1u) & 63u;
+            const uint32_t rem = lane_value(cs_rem, tl);
+            const double wv = lane_value(cs_m, tl);
+            wm = __builtin_amdgcn_frexp_mant(wv);
+            we = (int)lane_value((uint32_t)cs_e, tl) + __builtin_amdgcn_frexp_exp(wv) + (int)vz;
+            asm volatile("" : "+v"(wm));
+            ekey = lane_value(cs_key, tl);
+            ra = lane_value(cs_ra, tl) + vz;
+            if (rem == 1u) sp -= 1u;           // its last copy: the entry is done
+            cs_rem -= (lane == (int)tl) ? 1u : 0u;
+            // LIFO deletion of the sites after it restores the table exactly
+            const uint32_t back = (ra >> 3) + (sid_base - rec_base / 8u);
+            clear_sites<Key>(lane2, sa - back, at * (uint32_t)sizeof(Key) + lds_address(table));
+            for (uint32_t d = 128u; __ballot(sa - back > d) != 0ull; d += 128u)
+                if (lane2 + d < sa - back)
+                    table[*(const __attribute__((address_space(3))) uint16_t*)(uintptr_t)(sa - d - lane2)] = (Key)0;
+            sa = back;
+            no_decision();
+            load_next();
+        };
+        // Runs common events, the enrichments that make two copies and the
+        // prunings, until an event needs more: false, the event at li is still
+        // to be handled; true, a copy ended and no pending one is in registers.
+        auto run_ahead = [&](auto decide) INLINE -> bool {
+            for (;;) {
+                scan(decide);
+                while (chosen()) {
+                    commit(w1);
+                    scan(decide);
+                }
+                if (li >= last) return false;
+                uint32_t pruned = 0u;          // or no free neighbour: a trap, no event
+                if (pick != 0ull) {
+                    if constexpr (decltype(decide)::value) {
+                        // (uu is the uniform itself where 1/16 or more is compared)
+                        if (__ballot(r < 1.0 && r >= 0.0625 && uu >= r) == 0ull) {
+                            // 1 <= r < 2 and u >= 2 - r: two copies
+                            if (__ballot(r >= 1.0 && r <= 1.9375 && ut == uu) == 0ull) return false;
+                            il = first_bit(pick);
+                            if (!chosen() || sp - lo == 64u) return false;
+                            push(0.5 * wm, 1u);
+                            commit(0.5 * wm);
+                            continue;
+                        }
+                        pruned = 1u;           // r < 1, pruned with probability 1 - r
+                    } else {
+                        return false;
+                    }
+                }
+                c_prunes += pruned;
+                c_traps += 1u - pruned;
+                li += pruned;
+                if (sp == lo) return true;
+                resume();
+            }
+        };
 
         for (;;) {
-            // ---- run ahead: common events, until one is not ----
-            // (what the event that stopped it needs is left in these)
-            Key nk;
-            uint32_t slot, a, x, ra = rec_base + n * 16u + vz, sa = sid_base + n * 2u + vz;
-            uint64_t hits;
-            Key v;
-            SumRec Gn;
-            uint32_t il;
-            const uint32_t li0 = li;
-            auto run_ahead = [&](auto decide) {
-                for (;;) {
-                    // occupancy reads, the next length's record and pooled sum
-                    nk = S_::next(ekey, pdelta);
-                    slot = slot_of(nk);
-                    v = lds_load<Key>(slot * (uint32_t)sizeof(Key) + lds_address(table));
-                    SumRec nx2 = {0.0, 0, 0u}, nr2 = {0.0, 0, 0u};
-                    if constexpr (LONG) {
-                        // (one length further: it has a whole step to arrive.  At
-                        // n_max - 1 that is past the last record: row is padded to
-                        // 16 records or the next array follows; never used)
-                        nx2 = load_global(reinterpret_cast<const SumRec*>(
-                            reinterpret_cast<const unsigned char*>(Ls) + ra) + 2);
-                        if constexpr (OBS)
-                            nr2 = load_global(reinterpret_cast<const SumRec*>(
-                                reinterpret_cast<const unsigned char*>(LRs) + ra) + 2);
-                    } else {
-                        nxt = record_of(lds_load<u32x4>(ra + 16u));
-                        if constexpr (OBS) nxr = record_of(lds_load<u32x4>(ra + 16u + row_lds));
+            bool bt = control_mode ? run_ahead(yes{}) : run_ahead(no{});
+            if (!bt && li == 64u) {
+                // ---- the next random blocks ----
+                kb += 63u;
+                li = 1u;
+                draw();
+                const XF w = xf_norm_nz(wm, we);
+                Lm = ldexp(Lm, we - w.e);
+                weigh(w);
+                arm(length());
+                continue;
+            }
+            uint32_t n = length();
+            if (!bt) {
+                // ---- one event with every case ----
+                uint64_t outside = 0ull;       // directions found outside their places (last lanes)
+                if (far_lo != ~0u) {
+                    for (uint32_t b = far_lo; b <= n; b += 64u) {
+                        const uint32_t i = b + (uint32_t)lane;
+                        const Key k = i <= n ? table[sid[i]] : (Key)0;
+                        for (int d = 0; d < 2 * D; ++d)
+                            if (__ballot(k == lane_value(nk, (uint32_t)(d * W))) != 0ull &&
+                                ((hits >> (d * W)) & FIELD) == 0ull)
+                                outside |= 1ull << (d * W + W - 1);
                     }
-                    Gn = pooled(ra + 16u);
-                    const uint32_t B0 = lane_value(b0, li);
-                    const double uu = lane_value(uf, li);
-                    // the next length's sum at this scale; the term that adds it
-                    // to u is below its last place unless the sum is 2^440 times
-                    // the weight or more, which stops here
-                    const double t = ldexp(nxt.m, nxt.e - we);
-                    const double ut = __builtin_fma(t, 0x1p-501, uu);
-                    double w1 = wm;
-                    uint64_t ok;
-                    if constexpr (decltype(decide)::value) {
-                        // eqn (6): r = W / [W_n], [W_n] = sum / seen (own epoch
-                        // data weighted N in Algorithm 2), as (W * seen) / sum.
-                        // One copy goes on iff u < r < 1 (a survivor, which takes
-                        // sum / seen) or 1 <= r < 2 and u < 2 - r.
-                        const double sum = ldexp(Gm, Ge - we) + Lm * pool;
-                        const double r = div_by(wm * seen, sum, recip_normal(sum));
-                        ok = __ballot(ut < min_f64(r, 2.0 - r));
-                        const double ws = div_by(sum, seen, seen_r);
-                        w1 = r < 1.0 ? ws : wm;
-                    } else {
-                        ok = __ballot(ut < 1.0);
-                    }
-                    hits = __ballot(v == nk);
-                    a = (uint32_t)(2 * D) - mask_count(hits);
-                    // The j-th free neighbour, j = floor(B0 a / 2^32): the number
-                    // of free directions below a lane's own is pdir less the hits
-                    // in lanes below it, so x is 0 in the chosen direction's
-                    // lanes (and in lanes of occupied neighbours of it: those up
-                    // to the hit, which are not empty, before it, those past the
-                    // hit after it).  Its first empty place is the lowest lane
-                    // with x = 0 that read an empty slot.
-                    const uint32_t j = __umulhi(B0, a);
-                    x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j - (uint32_t)pdir));
-                    const uint64_t pick = __ballot((x | S_::mark(v)) == 0u) & ok;
-                    if (pick == 0ull) break;             // also where no neighbour is free
-                    il = (uint32_t)__builtin_ctzll(pick);
-                    if ((BLANK >> il) & 1ull) break;     // all places taken
-                    // grow: W *= a_+, eqn (2), and record, eqn (4)
-                    wm = w1 * (double)a;
-                    Lm = t + wm;
-                    write_arrival<LONG>(il, slot * (uint32_t)sizeof(Key) + lds_address(table), nk, sa, slot, ra,
-                                        words_of(Lm, we, nxt.h + 1u), Ls);
-                    ekey = lane_value(nk, il);
-                    if constexpr (OBS) {
-                        // R^2 of the new end, exact in FP64 (|coordinates| < 2^15)
-                        int cx, cy, cz;
-                        S_::unpack(ekey, cx, cy, cz);
-                        const double r2 = (double)cx * (double)cx + (double)cy * (double)cy +
-                                          (double)cz * (double)cz;
-                        SumRec rr;
-                        rr.m = ldexp(nxr.m, nxr.e - we) + wm * r2;
-                        rr.e = we;
-                        rr.h = 0u;
-                        if (lane == 0) {
-                            if constexpr (LONG)
-                                store_global(reinterpret_cast<SumRec*>(reinterpret_cast<unsigned char*>(LRs) + ra) + 1,
-                                             rr);
-                            else
-                                *reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds + (ra - rec_base) + 16u) = rr;
+                }
+                const uint32_t au = (uint32_t)(2 * D) - (uint32_t)__popcll(hits | outside);
+                XF w = xf_norm_nz(wm, we);
+                if (au == 0u) {
+                    c_traps += 1u;
+                    bt = true;
+                } else if (control_mode && __ballot(Lm != 0.0) != 0ull) {
+                    const SumRec here = rec_ld(Ls + (n + vz));
+                    const XF sum = xf_add_nz(XF{Gm, Ge}, xf_mul_nz(xf_norm_nz(here.m, here.e), pool));
+                    const double rr = xf_ratio_nz(xf_mul_nz(w, seen), sum);
+                    const double ul = lane_value(u, li);
+                    const double f = floor(rr);
+                    // floor(r) as an integer: r > 0, and r <= seen / N < 2^32 because
+                    // the sum includes N times the walk's own weight (the clamp
+                    // only keeps the conversion defined); r >= 1 iff fi >= 1
+                    const uint32_t fi = ufirst((uint32_t)__builtin_fmin(f, 4294967295.0));
+                    if (fi >= 1u) {
+                        // r >= 1: c = floor(r) with probability ceil(r) - r, else
+                        // ceil(r) (r integral: u < 1)
+                        const uint32_t ci = ubool(ul < (f + 1.0) - rr) ? fi : fi + 1u;
+                        if (ci > 1u) {
+                            w = xf_div_nz(w, (double)ci);
+                            weigh(w);
+                            if (sp - lo == 64u) {
+                                // every lane holds an entry: the oldest one moves
+                                // to its place in global memory
+                                if (lane == (int)(lo & 63u)) {
+                                    StackEntry e;
+                                    e.n = cs_ra;
+                                    e.remaining = cs_rem;
+                                    e.e = cs_e;
+                                    e.pad0 = 0u;
+                                    e.m = cs_m;
+                                    e.key = (uint64_t)cs_key;
+                                    store_global(stk + lo, e);
+                                }
+                                lo += 1u;
+                            }
+                            push(wm, ci - 1u);
                         }
+                    } else if (ubool(ul < rr)) {
+                        w = xf_div_nz(sum, seen);  // r < 1, survives: W / r
+                    } else {
+                        c_prunes += 1u;            // r < 1, pruned with probability 1 - r
+                        li += 1u;
+                        bt = true;
                     }
-                    digest = (digest ^ ((il >> LW) | (a << 3))) * FNV_PRIME;
-                    Gm = Gn.m;
-                    Ge = Gn.e;
+                }
+                if (!bt) {
+                    if (far_lo != ~0u) {
+                        const uint64_t occ = hits | outside;
+                        const uint32_t j = __umulhi(lane_value(b0, li), au);
+                        x = __builtin_amdgcn_mbcnt_hi((uint32_t)(occ >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)occ, j - (uint32_t)pdir));
+                    }
+                    il = (uint32_t)__builtin_ctzll(__ballot((x | S_::mark(v)) == 0u) & ~outside);
+                    ekey = lane_value(nk, il);
+                    uint32_t ins = lane_value(slot, il);
+                    if (!chosen()) {
+                        // all places taken: the first empty slot of the table
+                        // (slots outnumber the sites of the longest walk)
+                        for (uint32_t b = 0;; b += 64u) {
+                            const uint32_t i = b + (uint32_t)lane;
+                            const uint64_t em =
+                                __ballot(i < sub * (uint32_t)(W - 1) && S_::empty(table[min(i, S - 1u)]));
+                            if (em != 0ull) {
+                                ins = b + (uint32_t)__builtin_ctzll(em);
+                                break;
+                            }
+                        }
+                        far_lo = min(far_lo, n + 1u);
+                    }
+                    digest = (digest ^ ((il >> LW) | (au << 3))) * FNV_PRIME;
+                    w = xf_mul_nz(w, (double)au);
+                    n += 1u;
                     ra += 16u;
                     sa += 2u;
                     li += 1u;
-                    if constexpr (LONG) {
-                        nxt = nx2;
-                        if constexpr (OBS) nxr = nr2;
+                    const XF Lnew = xf_add_nz(xf_of(nxt), w);
+                    SumRec nr;
+                    nr.m = Lnew.m;
+                    nr.e = Lnew.e;
+                    nr.h = nxt.h + 1u;
+                    if (lane == 0) {
+                        table[ins] = ekey;
+                        sid[n] = (uint16_t)ins;
+                        rec_st(Ls + n, nr);
                     }
-                }
-            };
-            if (control_mode) run_ahead(yes{});
-            else run_ahead(no{});
-            n += li - li0;
-            c_steps += li - li0;
-            control = (li != li0) ? control_mode : control;
-
-            // ---- the event that stopped it ----
-            uint64_t outside = 0ull;           // directions found outside their places (last lanes)
-            if (far_lo != ~0u) {
-                for (uint32_t b = far_lo; b <= n; b += 64u) {
-                    const uint32_t i = b + (uint32_t)lane;
-                    const Key k = i <= n ? table[sid[i]] : (Key)0;
-#pragma unroll
-                    for (int d = 0; d < 2 * D; ++d)
-                        if (__ballot(k == lane_value(nk, d * W)) != 0ull && ((hits >> (d * W)) & FIELD) == 0ull)
-                            outside |= 1ull << (d * W + W - 1);
-                }
-            }
-            const uint32_t au = (uint32_t)(2 * D) - (uint32_t)__popcll(hits | outside);
-            bool bt = false, pruned = false;
-            XF w = xf_norm_nz(wm, we);
-            if (au == 0u) {
-                cv += (lane == ST_TRAPS) ? 1ull : 0ull;
-                bt = true;
-            } else if (control) {
-                // the decision in full
-                const SumRec here = rec_ld(Ls + (n + vz));
-                const XF sum = xf_add_nz(XF{Gm, Ge}, xf_mul_nz(xf_norm_nz(here.m, here.e), pool));
-                const double r = xf_ratio_nz(xf_mul_nz(w, seen), sum);
-                const double ul = lane_value(u, li);
-                const double f = floor(r);
-                // floor(r) as an integer: r > 0, and r <= seen / N < 2^32 because
-                // the sum includes N times the walk's own weight (the clamp
-                // only keeps the conversion defined); r >= 1 iff fi >= 1
-                const uint32_t fi = ufirst((uint32_t)__builtin_fmin(f, 4294967295.0));
-                if (fi >= 1u) {
-                    // r >= 1: c = floor(r) with probability ceil(r) - r, else ceil(r)
-                    // (r integral: u < 1)
-                    const uint32_t ci = ubool(ul < (f + 1.0) - r) ? fi : fi + 1u;
-                    if (ci > 1u) {
-                        w = xf_div_nz(w, (double)ci);
-                        if (sp - lo == 64u) {
-                            // every lane holds an entry: the oldest one moves
-                            // to its place in global memory
-                            if (lane == (int)(lo & 63u)) {
-                                StackEntry e;
-                                e.n = cs_n;
-                                e.remaining = cs_rem;
-                                e.e = cs_e;
-                                e.pad0 = 0u;
-                                e.m = cs_m;
-                                e.key = (uint64_t)cs_key;
-                                store_global(stk + lo, e);
-                            }
-                            lo += 1u;
-                        }
-                        // the new entry: ci - 1 copies still to resume at (n, W / ci)
-                        const bool mine = lane == (int)(sp & 63u);
-                        cs_n = mine ? n : cs_n;
-                        cs_rem = mine ? ci - 1u : cs_rem;
-                        cs_e = mine ? w.e : cs_e;
-                        cs_m = mine ? w.m : cs_m;
-                        cs_key = mine ? ekey : cs_key;
-                        sp += 1;
-                        c_maxd = (sp > c_maxd) ? sp : c_maxd;
-                        cv += (lane == ST_ENRICH) ? 1ull
-                              : ((lane == ST_COPIES) ? (uint64_t)(ci - 1u) : 0ull);
+                    if constexpr (OBS) {
+                        int cx, cy, cz;
+                        S_::unpack(ekey, cx, cy, cz);
+                        const double r2 =
+                            (double)cx * (double)cx + (double)cy * (double)cy + (double)cz * (double)cz;
+                        const XF R = xf_add_nz(xf_of(nxr), xf_mul_nz(w, r2));
+                        SumRec ro;
+                        ro.m = R.m;
+                        ro.e = R.e;
+                        ro.h = 0u;
+                        if (lane == 0) rec_st(LRs + n, ro);
                     }
-                } else if (ubool(ul < r)) {
-                    w = xf_div_nz(sum, seen);  // r < 1, survives: W / r
-                } else {
-                    pruned = true;             // r < 1, pruned with probability 1 - r
-                }
-            }
-            if (pruned) {
-                cv += (lane == ST_PRUNES) ? 1ull : 0ull;
-                li += 1u;
-                bt = true;
-            } else if (!bt) {
-                // ---- growth, as above, with every case of the sums and the table ----
-                if (far_lo != ~0u) {
-                    const uint64_t occ = hits | outside;
-                    const uint32_t j = __umulhi(lane_value(b0, li), au);
-                    x = __builtin_amdgcn_mbcnt_hi((uint32_t)(occ >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)occ, j - (uint32_t)pdir));
-                }
-                il = (uint32_t)__builtin_ctzll(__ballot((x | S_::mark(v)) == 0u) & ~outside);
-                ekey = lane_value(nk, il);
-                uint32_t ins = lane_value(slot, il);
-                if ((BLANK >> il) & 1ull) {
-                    // all places taken: the first empty slot of the table
-                    // (slots outnumber the sites of the longest walk)
-                    for (uint32_t b = 0;; b += 64u) {
-                        const uint32_t i = b + (uint32_t)lane;
-                        const uint64_t em =
-                            __ballot(i < sub * (uint32_t)(W - 1) && S_::empty(table[min(i, S - 1u)]));
-                        if (em != 0ull) {
-                            ins = b + (uint32_t)__builtin_ctzll(em);
-                            break;
-                        }
+                    wave_fence();
+                    if (steps() >= capv) {
+                        abort = true;
+                        break;
                     }
-                    far_lo = min(far_lo, n + 1u);
+                    // (a sum out of this weight's range makes the ratio 0 or no
+                    // number, and the decision comes here)
+                    weigh(w);
+                    Lm = ldexp(Lnew.m, Lnew.e - we);
+                    Gm = Gn.m;
+                    Ge = Gn.e;
+                    load_next();
+                    bt = n == n_max;
                 }
-                digest = (digest ^ ((il >> LW) | (au << 3))) * FNV_PRIME;
-                w = xf_mul_nz(w, (double)au);
-                n += 1u;
-                c_steps += 1u;
-                const XF Lnew = xf_add_nz(xf_of(nxt), w);
-                SumRec nr;
-                nr.m = Lnew.m;
-                nr.e = Lnew.e;
-                nr.h = nxt.h + 1u;
-                if (lane == 0) {
-                    table[ins] = ekey;
-                    sid[n] = (uint16_t)ins;
-                    rec_st(Ls + n, nr);
-                }
-                if constexpr (OBS) {
-                    int cx, cy, cz;
-                    S_::unpack(ekey, cx, cy, cz);
-                    const double r2 = (double)cx * (double)cx + (double)cy * (double)cy + (double)cz * (double)cz;
-                    const XF R = xf_add_nz(xf_of(nxr), xf_mul_nz(w, r2));
-                    SumRec rr;
-                    rr.m = R.m;
-                    rr.e = R.e;
-                    rr.h = 0u;
-                    if (lane == 0) rec_st(LRs + n, rr);
-                }
-                wave_fence();
-                li += 1u;
-                if (c_steps >= capv) {
-                    abort = true;
-                    break;
-                }
-                // (a sum out of this weight's range makes the ratio 0 or no
-                // number, and the decision is made here)
-                start_at(w);
-                Lm = ldexp(Lnew.m, Lnew.e - we);
-                Gm = Gn.m;
-                Ge = Gn.e;
-                control = control_mode;
-                bt = n == n_max;
             }
             if (bt) {
                 // ---- resume the most recent pending copy, or end the tour ----
@@ -1329,7 +1441,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
                     const uint32_t q = base + (((uint32_t)lane - base) & 63u);
                     if (q < sp) {
                         const StackEntry e = load_global(stk + q);
-                        cs_n = e.n;
+                        cs_ra = e.n;
                         cs_rem = e.remaining;
                         cs_e = e.e;
                         cs_m = e.m;
@@ -1337,35 +1449,23 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
                     }
                     lo = base;
                 }
-                const uint32_t tl = (sp - 1u) & 63u;
-                const uint32_t rn = lane_value(cs_n, tl);
-                const uint32_t rem = lane_value(cs_rem, tl);
-                start_at(XF{lane_value(cs_m, tl), (int32_t)lane_value((uint32_t)cs_e, tl)});
-                ekey = (Key)lane_value(cs_key, tl);
-                if (rem == 1u) sp -= 1u;       // its last copy: the entry is done
-                else cs_rem -= (lane == (int)tl) ? 1u : 0u;
-                // LIFO deletion of sites rn+1..n restores the table exactly
-                for (uint32_t i = rn + 1u + (uint32_t)lane; i <= n; i += 64u) table[sid[i]] = (Key)0;
-                n = rn;
+                resume();
+                n = length();
                 if (far_lo > n) far_lo = ~0u;
-                no_decision();
-                wave_fence();
             }
-            if (li == 64u) {
-                kb += 64u;
-                li = 0u;
-                draw();
-            }
-            arm();
+            arm(n);
         }
         // end of the tour (or abort): back to the empty walk
-        c_events += kb + li;
+        c_events += kb + li - 1u;
+        const uint32_t n = length();
         for (uint32_t i = 1u + (uint32_t)lane; i <= n; i += 64u) table[sid[i]] = (Key)0;
         wave_fence();
     }
-    cv += (lane == ST_EVENTS) ? c_events : 0ull;
+    // (read again, so that the steps need not keep what only the end uses)
+    asm volatile("" : "+s"(desc));
+    const ProblemDesc Q = load_const(desc);
     // the sums leave normalised (m in [0.5, 1), or 0 with e = 0)
-    auto leave = [&](SumRec* p, SumRec* out) {
+    auto leave = [&](SumRec* p, SumRec* out) INLINE {
         SumRec r = rec_ld(p);
         const XF v = xf_norm(r.m, r.e);
         r.m = v.m;
@@ -1375,25 +1475,28 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
     };
     if (lane == 0) rec_st(Ls, rec0);
     wave_fence();
-    for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) {
-        leave(Ls + i, Lrow + i);
-        if constexpr (OBS) leave(LRs + i, P.LR + rb0 + i);
+#pragma unroll 1
+    for (uint32_t i = (uint32_t)lane; i <= Q.n_max; i += 64u) {
+        leave(Ls + i, Q.L + (size_t)s * Q.row + i);
+        if constexpr (OBS) leave(LRs + i, Q.LR + (size_t)s * Q.row + i);
     }
     wave_fence();
     if (lane == 0) {
-        if (abort) atomicOr(&P.ctrl[CTRL_ERR], ERR_CAP);
-        uint64_t* sr = P.stats + (size_t)s * STATS_WORDS;
-        P.t[s] = t0 + c_tours;
-        P.m[s] = m;
-        sr[ST_STEPS] += c_steps;
+        if (abort) atomicOr(&Q.ctrl[CTRL_ERR], ERR_CAP);
+        uint64_t* sr = Q.stats + (size_t)s * STATS_WORDS;
+        Q.t[s] += c_tours;
+        Q.m[s] = m;
+        sr[ST_STEPS] += (uint32_t)c_events - c_prunes;
         sr[ST_TOURS] += c_tours;
         if (c_maxd > sr[ST_MAXDEPTH]) sr[ST_MAXDEPTH] = c_maxd;
         sr[ST_DIGEST] = digest;
         if (abort) sr[ST_CAPPED] = 1;
     }
-    if (lane == ST_EVENTS || lane == ST_ENRICH || lane == ST_COPIES || lane == ST_PRUNES ||
-        lane == ST_TRAPS)
-        P.stats[(size_t)s * STATS_WORDS + lane] += cv;
+    if (lane >= ST_EVENTS && lane <= ST_TRAPS) {
+        const uint64_t c = lane == ST_EVENTS ? c_events : lane == ST_ENRICH ? c_enrich : lane == ST_COPIES ? c_copies
+                           : lane == ST_PRUNES ? c_prunes : c_traps;
+        Q.stats[(size_t)s * STATS_WORDS + lane] += c;
+    }
     return c_tours | (abort ? WALK_ABORTED : 0u);
 }
 
@@ -1401,6 +1504,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc& P, uint32_t
 // each wavefront takes the next item from a device queue until none is left.
 // A problem alone is a batch of one, so a problem's bits do not depend on what
 // else shares the launch.
+// (at most 128 VGPRs: four waves per SIMD)
+#define WAVES4 __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+
 template <bool OBS, bool LONG>
 __device__ __forceinline__ void batch_body(const BatchArgs& B) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -1425,19 +1531,19 @@ __device__ __forceinline__ void batch_body(const BatchArgs& B) {
         // make every field (and so the whole walk's control flow) non-uniform
         const ProblemDesc P = load_const(E.desc);
         const uint32_t s = item - E.first_item;
-        if (P.dim == 2) walk_sequence<2, OBS, LONG>(P, E.tours, E.step_cap, s, lds, P.G, false);
-        else if (!OBS && P.ckey) walk_sequence<3, false, LONG, true>(P, E.tours, E.step_cap, s, lds, P.G, false);
-        else walk_sequence<3, OBS, LONG>(P, E.tours, E.step_cap, s, lds, P.G, false);
+        if (P.dim == 2) walk_sequence<2, OBS, LONG>(E.desc, E.tours, E.step_cap, s, lds, P.G, false);
+        else if (!OBS && P.ckey) walk_sequence<3, false, LONG, true>(E.desc, E.tours, E.step_cap, s, lds, P.G, false);
+        else walk_sequence<3, OBS, LONG>(E.desc, E.tours, E.step_cap, s, lds, P.G, false);
     }
 }
 
-__global__ void __launch_bounds__(64) batch_kernel(BatchArgs B) { batch_body<false, false>(B); }
+__global__ void WAVES4 batch_kernel(BatchArgs B) { batch_body<false, false>(B); }
 
 // The same for one problem whose walks also record W * R^2, whose walks are
 // long (sums in global memory), or both.
-__global__ void __launch_bounds__(64) batch_obs_kernel(BatchArgs B) { batch_body<true, false>(B); }
-__global__ void __launch_bounds__(64) batch_long_kernel(BatchArgs B) { batch_body<false, true>(B); }
-__global__ void __launch_bounds__(64) batch_long_obs_kernel(BatchArgs B) { batch_body<true, true>(B); }
+__global__ void WAVES4 batch_obs_kernel(BatchArgs B) { batch_body<true, false>(B); }
+__global__ void WAVES4 batch_long_kernel(BatchArgs B) { batch_body<false, true>(B); }
+__global__ void WAVES4 batch_long_obs_kernel(BatchArgs B) { batch_body<true, true>(B); }
 
 // ---------------------------------------------------------------------------
 // Device-side epoch chaining.  Every problem runs its whole epoch schedule in
@@ -1632,7 +1738,7 @@ __device__ void job_merge(const JobArgs& A, const JobProblem& J, const ProblemDe
 
 // (at most 128 VGPRs: four waves per SIMD; the register pressure this adds
 // costs two spills in a chained item's merge part, none in the step loop)
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) job_kernel(JobArgs A) {
+__global__ void WAVES4 job_kernel(JobArgs A) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = (int)threadIdx.x;
     uint64_t idle_since = __builtin_amdgcn_s_memrealtime();
@@ -1722,13 +1828,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) jo
         const SumRec* Gsrc = (e == 0u) ? P.G : J.gver + (size_t)(e - 1u) * (P.row + JOB_GAP);
         uint32_t rv;
         if (J.lng)
-            rv = (P.dim == 2) ? walk_sequence<2, false, true>(P, tours, cap, s, lds, Gsrc, true)
-                 : P.ckey     ? walk_sequence<3, false, true, true>(P, tours, cap, s, lds, Gsrc, true)
-                              : walk_sequence<3, false, true>(P, tours, cap, s, lds, Gsrc, true);
+            rv = (P.dim == 2) ? walk_sequence<2, false, true>(J.desc, tours, cap, s, lds, Gsrc, true)
+                 : P.ckey     ? walk_sequence<3, false, true, true>(J.desc, tours, cap, s, lds, Gsrc, true)
+                              : walk_sequence<3, false, true>(J.desc, tours, cap, s, lds, Gsrc, true);
         else
-            rv = (P.dim == 2) ? walk_sequence<2>(P, tours, cap, s, lds, Gsrc, true)
-                 : P.ckey     ? walk_sequence<3, false, false, true>(P, tours, cap, s, lds, Gsrc, true)
-                              : walk_sequence<3>(P, tours, cap, s, lds, Gsrc, true);
+            rv = (P.dim == 2) ? walk_sequence<2>(J.desc, tours, cap, s, lds, Gsrc, true)
+                 : P.ckey     ? walk_sequence<3, false, false, true>(J.desc, tours, cap, s, lds, Gsrc, true)
+                              : walk_sequence<3>(J.desc, tours, cap, s, lds, Gsrc, true);
         if ((rv & WALK_ABORTED) && lane == 0)
             __hip_atomic_fetch_or(&A.state[pi].failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         job_merge(A, J, P, pi, e, s, rv & ~WALK_ABORTED, lds);
