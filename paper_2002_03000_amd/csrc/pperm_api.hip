@@ -801,7 +801,7 @@ uint32_t pow2_at_least(uint32_t n) {
 // per-epoch copies of its pooled sums and its merge-tree flags.
 struct JobLayout {
     uint64_t probs, state, order, counters, results, total;
-    std::vector<uint64_t> sched, gver, flags, stage, stage_m;
+    std::vector<uint64_t> sched, gver, flags, stage;
 };
 
 void job_layout(pperm_ctx* const* ctxs, const uint32_t* epochs, size_t count, JobLayout* L) {
@@ -820,14 +820,12 @@ void job_layout(pperm_ctx* const* ctxs, const uint32_t* epochs, size_t count, Jo
     L->gver.assign(count, 0);
     L->flags.assign(count, 0);
     L->stage.assign(count, 0);
-    L->stage_m.assign(count, 0);
     for (size_t i = 0; i < count; ++i) {
         const pperm_ctx* x = ctxs[i];
         L->sched[i] = take((uint64_t)epochs[i] * 4);
         L->gver[i] = take((uint64_t)epochs[i] * (x->lay.row + JOB_GAP) * sizeof(SumRec));
         L->flags[i] = take((uint64_t)pow2_at_least(x->cfg.n_sequences) * 4);
         L->stage[i] = take((uint64_t)x->cfg.n_sequences * sizeof(SumRec));
-        L->stage_m[i] = take((uint64_t)x->cfg.n_sequences * 4);
     }
     L->total = off;
 }
@@ -970,7 +968,6 @@ int run_job_impl(pperm_ctx* const* ctxs, const uint32_t* const* schedules, const
         J.result = reinterpret_cast<uint32_t*>(ws + L.results) + 4 * i;
         if (limits) {
             J.stage = reinterpret_cast<SumRec*>(ws + L.stage[i]);
-            J.stage_m = reinterpret_cast<uint32_t*>(ws + L.stage_m[i]);
             J.gsum = at<SumRec>(x, x->lay.groups);
             J.target = limits[i].target_rel_err;
             J.cap = limits[i].tour_cap;

@@ -152,8 +152,7 @@ struct JobProblem {
     uint32_t prio;            // issue priority 0..3 of its waves (longest chains highest)
     uint32_t lng;             // 1: long walks, the sequences' sums live in global memory
     // stop rule (evaluated after every merge; stage == nullptr: none)
-    SumRec* stage;            // [N] each sequence's record at n_max in the open epoch
-    uint32_t* stage_m;        // [N] its tours in the open epoch
+    SumRec* stage;            // [N] each sequence's record at n_max in the open epoch (h: its tours)
     SumRec* gsum;             // the context's 16 group sums, then 16 u64 group tours
     uint32_t* result;         // [4]: epochs done, stop reason (1 target, 2 cap), rel. error (2 words)
     double target;            // relative-error target, 0: none
@@ -163,12 +162,14 @@ struct JobProblem {
 // Per-problem scheduling word: (epoch << 32) | sequences claimed in it; the
 // tours of the epoch's finished sequences; and a flag raised when one of the
 // problem's sequences hit its step cap (the problem then stops after that
-// epoch).
-struct JobState {
+// epoch).  The word, which waiting waves poll, has a 128-byte line of its own.
+struct __attribute__((aligned(256))) JobState {
     unsigned long long word;
+    uint32_t pad[30];
     uint32_t msum;
     uint32_t failed;
 };
+static_assert(sizeof(JobState) == 256, "two lines");
 
 // Counter words of a chained launch (at offset 0 of its workspace):
 // problems finished per LDS class, items completed, problems stopped by a

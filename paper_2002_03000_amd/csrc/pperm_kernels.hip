@@ -656,6 +656,44 @@ __device__ __forceinline__ void store_global(T* p, const T& v) {
 }
 
 // ---------------------------------------------------------------------------
+// Memory that waves of one launch hand to each other (the chained launch).  The
+// eight XCDs have an L2 each, and a fence at agent scope writes back or
+// invalidates all of one, so what is handed over is written and read past the
+// L2 instead (relaxed atomics at agent scope, which need no fence), and a wave
+// announces its writes once they have arrived.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint64_t shared_load(const uint64_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t shared_load(const uint32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void shared_store(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void shared_store(uint32_t* p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Records and stack entries, 64 bits at a time.
+template <typename T>
+__device__ __forceinline__ T shared_load_as(const T* p) {
+    static_assert(sizeof(T) % 8 == 0, "whole 64-bit words");
+    uint64_t w[sizeof(T) / 8];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 8; ++i) w[i] = shared_load(reinterpret_cast<const uint64_t*>(p) + i);
+    return __builtin_bit_cast(T, w);
+}
+template <typename T>
+__device__ __forceinline__ void shared_store_as(T* p, const T& v) {
+    struct Words { uint64_t w[sizeof(T) / 8]; };
+    const Words w = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 8; ++i) shared_store(reinterpret_cast<uint64_t*>(p) + i, w.w[i]);
+}
+// Waits until this wave's writes have arrived.
+__device__ __forceinline__ void writes_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// ---------------------------------------------------------------------------
 // Sites of the wave walker.  A site's key is a linear function of its
 // coordinates (modulo 2^32 per word), so a neighbour's key is the end's key
 // plus a per-direction offset, and no key a walk can meet is 0 (an empty slot).
@@ -850,10 +888,11 @@ __device__ __forceinline__ void clear_sites(uint32_t index, uint32_t depth, uint
 
 // One sequence's `tours` tours against frozen pooled sums (the whole hot path
 // of one walk); run by one wavefront.  Gsrc: the pooled sums to read (the
-// problem's own, or an epoch's copy in a chained launch); fresh: the epoch
-// starts here, so the sequence's sums and tour count start from zero instead
-// of being read.  Returns the tours run, with bit 31 set if the step cap
-// stopped the sequence (WALK_ABORTED).
+// problem's own, or an epoch's copy in a chained launch).  Returns the tours
+// run, with bit 31 set if the step cap stopped the sequence (WALK_ABORTED).
+// JOB: a chained launch, where the epoch starts here (the sequence's sums and
+// tour count start from zero), its sums stay where they are (in LDS, or with
+// LONG in the global row) and another wave may have run its last epoch.
 // OBS: also record W * R^2 (squared end-to-end distance) at every arrival
 // beside the weight, the numerator of the ratio estimator of eqn (5).
 // LONG: walks too long for the per-length sums to share LDS with the
@@ -879,10 +918,10 @@ __device__ __forceinline__ void clear_sites(uint32_t index, uint32_t depth, uint
 //   256 Rosenbluth walks of up to 6000 cubic steps, twice   6.41 / 3.40 / 2.15
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 
-template <int D, bool OBS = false, bool LONG = false, bool CK = false>
+template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false>
 __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint32_t tours, uint32_t cap,
-                                                  uint32_t s, unsigned char* lds, const SumRec* Gsrc,
-                                                  bool fresh) {
+                                                  uint32_t s, unsigned char* lds, const SumRec* Gsrc) {
+    static_assert(!(OBS && JOB), "chained launches keep no observables");
     const ProblemDesc P = load_const(desc);
     static_assert(!(OBS && CK), "observables need coordinates, which compact keys do not keep");
     using S_ = typename SiteOf<D, CK>::T;
@@ -963,30 +1002,20 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
 
     // the copy stack of sequence s
     StackEntry* stk = P.stack + (size_t)s * n_max;
-    uint64_t MGs = shared_mode ? P.MG[0] : 0ull;
+    uint64_t MGs = 0ull;
+    if (shared_mode) MGs = JOB ? ufirst64(shared_load(P.MG)) : P.MG[0];
 
     const size_t rb0 = (size_t)s * row;
-    SumRec* __restrict__ Lrow = P.L + rb0;
     const SumRec* Grow = shared_mode ? Gsrc : Gsrc + rb0;
     if (!shared_mode) MGs = ufirst64(P.MG[s]);
-    uint32_t tlo = ufirst((uint32_t)P.t[s]);               // tour index: its low word keys the random numbers
-    uint32_t m = fresh ? 0u : ufirst(P.m[s]);
-    if constexpr (!LONG) {
-        if (fresh) {
-            const SumRec z = {0.0, 0, 0u};
-            for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) Ls[i] = z;
-        } else {
-            for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) Ls[i] = load_global(Lrow + i);
-        }
+    uint32_t tlo = ufirst((uint32_t)(JOB ? shared_load(P.t + s) : P.t[s]));   // tour index: its low word keys the random numbers
+    uint32_t m = JOB ? 0u : ufirst(P.m[s]);
+    if constexpr (JOB) {
+        for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) rec_st(Ls + i, SumRec{0.0, 0, 0u});
+    } else if constexpr (!LONG) {
+        for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) Ls[i] = load_global(P.L + rb0 + i);
         if constexpr (OBS) {
             for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) LRs[i] = load_global(P.LR + rb0 + i);
-        }
-    } else if (fresh) {
-        // the sums live in the global row: an epoch that starts here clears it
-        const SumRec z = {0.0, 0, 0u};
-        for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) store_global(Lrow + i, z);
-        if constexpr (OBS) {
-            for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) store_global(P.LR + rb0 + i, z);
         }
     }
     wave_fence();
@@ -997,7 +1026,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     uint32_t c_tours = 0, c_maxd = 0, c_enrich = 0, c_prunes = 0, c_traps = 0;
     uint64_t c_copies = 0, c_events = 0;
     const uint32_t capv = cap ? cap : 0xFFFFFFFFu;   // step cap of this call (0: none)
-    uint32_t digest = (uint32_t)P.stats[(size_t)s * STATS_WORDS + ST_DIGEST] + vz;
+    const uint64_t* old_digest = P.stats + (size_t)s * STATS_WORDS + ST_DIGEST;
+    uint32_t digest = (uint32_t)(JOB ? shared_load(old_digest) : *old_digest) + vz;
     bool abort = false;
     // the registers of the copy stack (see the tour loop)
     uint32_t cs_ra = 0u, cs_rem = 0u;
@@ -1350,7 +1380,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                                     e.pad0 = 0u;
                                     e.m = cs_m;
                                     e.key = (uint64_t)cs_key;
-                                    store_global(stk + lo, e);
+                                    if constexpr (JOB) shared_store_as(stk + lo, e);
+                                    else store_global(stk + lo, e);
                                 }
                                 lo += 1u;
                             }
@@ -1440,7 +1471,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     const uint32_t base = sp > 64u ? sp - 64u : 0u;
                     const uint32_t q = base + (((uint32_t)lane - base) & 63u);
                     if (q < sp) {
-                        const StackEntry e = load_global(stk + q);
+                        StackEntry e;
+                        if constexpr (JOB) e = shared_load_as(stk + q);
+                        else e = load_global(stk + q);
                         cs_ra = e.n;
                         cs_rem = e.remaining;
                         cs_e = e.e;
@@ -1470,8 +1503,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         const XF v = xf_norm(r.m, r.e);
         r.m = v.m;
         r.e = v.e;
-        if constexpr (!LONG) *p = r;
-        store_global(out, r);
+        if constexpr (JOB) rec_st(p, r);
+        else store_global(out, r);
     };
     if (lane == 0) rec_st(Ls, rec0);
     wave_fence();
@@ -1483,19 +1516,30 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     wave_fence();
     if (lane == 0) {
         if (abort) atomicOr(&Q.ctrl[CTRL_ERR], ERR_CAP);
-        uint64_t* sr = Q.stats + (size_t)s * STATS_WORDS;
-        Q.t[s] += c_tours;
-        Q.m[s] = m;
-        sr[ST_STEPS] += (uint32_t)c_events - c_prunes;
-        sr[ST_TOURS] += c_tours;
-        if (c_maxd > sr[ST_MAXDEPTH]) sr[ST_MAXDEPTH] = c_maxd;
-        sr[ST_DIGEST] = digest;
-        if (abort) sr[ST_CAPPED] = 1;
+        if constexpr (JOB) {
+            shared_store(Q.t + s, shared_load(Q.t + s) + c_tours);
+        } else {
+            Q.t[s] += c_tours;
+            Q.m[s] = m;
+        }
     }
-    if (lane >= ST_EVENTS && lane <= ST_TRAPS) {
-        const uint64_t c = lane == ST_EVENTS ? c_events : lane == ST_ENRICH ? c_enrich : lane == ST_COPIES ? c_copies
-                           : lane == ST_PRUNES ? c_prunes : c_traps;
-        Q.stats[(size_t)s * STATS_WORDS + lane] += c;
+    if (lane < STATS_WORDS) {
+        // lane i: word i of the sequence's counters
+        uint64_t* w = Q.stats + (size_t)s * STATS_WORDS + lane;
+        const uint64_t old = JOB ? shared_load(w) : *w;
+        uint64_t c = old;
+        c += lane == ST_STEPS ? (uint32_t)c_events - c_prunes : 0u;
+        c += lane == ST_EVENTS ? c_events : 0ull;
+        c += lane == ST_ENRICH ? c_enrich : 0u;
+        c += lane == ST_COPIES ? c_copies : 0ull;
+        c += lane == ST_PRUNES ? c_prunes : 0u;
+        c += lane == ST_TRAPS ? c_traps : 0u;
+        c += lane == ST_TOURS ? c_tours : 0u;
+        if (lane == ST_MAXDEPTH && c < c_maxd) c = c_maxd;
+        if (lane == ST_DIGEST) c = digest;
+        if (lane == ST_CAPPED && abort) c = 1;
+        if constexpr (JOB) shared_store(w, c);
+        else *w = c;
     }
     return c_tours | (abort ? WALK_ABORTED : 0u);
 }
@@ -1531,9 +1575,9 @@ __device__ __forceinline__ void batch_body(const BatchArgs& B) {
         // make every field (and so the whole walk's control flow) non-uniform
         const ProblemDesc P = load_const(E.desc);
         const uint32_t s = item - E.first_item;
-        if (P.dim == 2) walk_sequence<2, OBS, LONG>(E.desc, E.tours, E.step_cap, s, lds, P.G, false);
-        else if (!OBS && P.ckey) walk_sequence<3, false, LONG, true>(E.desc, E.tours, E.step_cap, s, lds, P.G, false);
-        else walk_sequence<3, OBS, LONG>(E.desc, E.tours, E.step_cap, s, lds, P.G, false);
+        if (P.dim == 2) walk_sequence<2, OBS, LONG>(E.desc, E.tours, E.step_cap, s, lds, P.G);
+        else if (!OBS && P.ckey) walk_sequence<3, false, LONG, true>(E.desc, E.tours, E.step_cap, s, lds, P.G);
+        else walk_sequence<3, OBS, LONG>(E.desc, E.tours, E.step_cap, s, lds, P.G);
     }
 }
 
@@ -1566,15 +1610,28 @@ __device__ __forceinline__ uint32_t job_finished(const JobArgs& A) {
     return done;
 }
 
-// Lane 0 tries to claim the next sequence of problem pi's open epoch.
+// Lane 0 tries to claim the next sequence of problem pi's open epoch.  An add
+// gives every wave that comes at once its own sequence in one round trip (with
+// a compare-and-swap one of them would succeed per round trip); it may run past
+// N, which the next epoch's word replaces.  Past the slice's end the claim must
+// not open an epoch, which only the compare-and-swap can refuse.
 __device__ __forceinline__ bool job_claim(const JobArgs& A, uint32_t pi, uint32_t epochs, uint32_t N,
                                           bool closed, uint32_t& e, uint32_t& s) {
-    unsigned long long w = __hip_atomic_load(&A.state[pi].word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long w;
+    if (!closed) {
+        w = __hip_atomic_fetch_add(&A.state[pi].word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        e = (uint32_t)(w >> 32);
+        s = (uint32_t)w;
+        asm volatile("" ::: "memory");       // (nothing of the epoch is read before it is claimed)
+        return e < epochs && s < N;
+    }
+    w = __hip_atomic_load(&A.state[pi].word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int attempt = 0; attempt < 8; ++attempt) {
         const uint32_t ee = (uint32_t)(w >> 32), cc = (uint32_t)w;
-        if (ee >= epochs || cc >= N || (closed && cc == 0u && ee > 0u)) return false;
-        if (__hip_atomic_compare_exchange_strong(&A.state[pi].word, &w, w + 1ull, __ATOMIC_ACQUIRE,
+        if (ee >= epochs || cc >= N || (cc == 0u && ee > 0u)) return false;
+        if (__hip_atomic_compare_exchange_strong(&A.state[pi].word, &w, w + 1ull, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            asm volatile("" ::: "memory");
             e = ee;
             s = cc;
             return true;
@@ -1584,71 +1641,92 @@ __device__ __forceinline__ bool job_claim(const JobArgs& A, uint32_t pi, uint32_
 }
 
 // The sequence's part of its epoch's merge, after its tours: sample counts,
-// tour count, and the climb up the merge tree.
+// tour count, and the climb up the merge tree.  A wave's partial sums stay in
+// its LDS row (a long walk's in its global row) and are written out, to the row
+// of its node's first leaf, only where the partner is not there yet; the second
+// to arrive adds the partner's.  12 problems of 256 sequences and 8 epochs,
+// whose longest chain of steps takes 21 ms: 207 ms with agent fences at every
+// node, claims by compare-and-swap and all waiting waves polling every 3 us,
+// 29.6 ms without.
 __device__ void job_merge(const JobArgs& A, const JobProblem& J, const ProblemDesc& P, uint32_t pi,
                           uint32_t e, uint32_t s, uint32_t tours_run, unsigned char* lds) {
     const int lane = (int)threadIdx.x;
     const uint32_t row = P.row, n1 = P.n_max + 1u;
-    // the sequence's sums of this epoch: in LDS, or (long walks) its global row,
-    // written by this same wave
-    const SumRec* Ls = J.lng ? P.L + (size_t)s * row : reinterpret_cast<const SumRec*>(lds + P.lds_team_bytes);
+    SumRec* Ls = reinterpret_cast<SumRec*>(lds + P.lds_team_bytes);
+    uint32_t l = 0, i = s;
+    // the partial sums of node (l, i)
+    auto node = [&](uint32_t ll, uint32_t ii) INLINE { return P.L + (size_t)(ii << ll) * row; };
+    auto own = [&](uint32_t n) INLINE -> SumRec { return J.lng ? shared_load_as(node(l, i) + n) : Ls[n]; };
+    if (J.lng) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     for (uint32_t n = (uint32_t)lane; n < n1; n += 64u)
-        __hip_atomic_fetch_add(&P.HG[n], (uint64_t)Ls[n].h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(&P.HG[n], (uint64_t)own(n).h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (lane == 0) {
         __hip_atomic_fetch_add(&A.state[pi].msum, tours_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        P.m[s] = 0u;
         if (J.stage != nullptr) {
-            // what the group sums of the stop rule need, before the tree overwrites the row
-            store_global(J.stage + s, Ls[P.n_max]);
-            J.stage_m[s] = tours_run;
+            // what the group sums of the stop rule need
+            SumRec r = own(P.n_max);
+            r.h = tours_run;
+            shared_store_as(J.stage + s, r);
         }
     }
-    uint32_t l = 0, i = s;
     for (;;) {
         if (l == J.levels) break;                         // at the root
         if (((i ^ 1u) << l) < J.N) {
             // the partner subtree has leaves: the second of the two goes on
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            uint32_t* flag = &J.flags[(J.p2 >> (l + 1u)) + (i >> 1)];
+            writes_arrived();
             uint32_t old = 0u;
-            if (lane == 0)
-                old = __hip_atomic_fetch_add(&J.flags[(J.p2 >> (l + 1u)) + (i >> 1)], 1u, __ATOMIC_ACQ_REL,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-            old = ufirst(__shfl(old, 0, 64));
-            if (old == 0u) return;                        // the partner will continue
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            if (lane == 0) J.flags[(J.p2 >> (l + 1u)) + (i >> 1)] = 0u;
-            SumRec* left = P.L + (size_t)((i & ~1u) << l) * row;
-            const SumRec* right = P.L + (size_t)((i | 1u) << l) * row;
+            if (!J.lng) {
+                if (lane == 0) old = shared_load(flag);
+                old = ufirst(__shfl(old, 0, 64));
+                if (old == 0u) {
+                    SumRec* mine = node(l, i);
+#pragma unroll 4
+                    for (uint32_t n = (uint32_t)lane; n < n1; n += 64u) shared_store_as(mine + n, Ls[n]);
+                    writes_arrived();
+                }
+            }
+            if (old == 0u) {
+                if (lane == 0)
+                    old = __hip_atomic_fetch_add(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                old = ufirst(__shfl(old, 0, 64));
+                if (old == 0u) return;                    // the partner will continue
+            }
+            asm volatile("" ::: "memory");
+            if (lane == 0) shared_store(flag, 0u);
+            const SumRec* other = node(l, i ^ 1u);
+            SumRec* both = node(l + 1u, i >> 1);
+#pragma unroll 4
             for (uint32_t n = (uint32_t)lane; n < n1; n += 64u) {
-                const SumRec a = load_global(left + n);
-                const SumRec b = load_global(right + n);
-                const XF v = xf_add(xf_of(a), xf_of(b));
+                const XF v = xf_add(xf_of(own(n)), xf_of(shared_load_as(other + n)));
                 SumRec r;
                 r.m = v.m;
                 r.e = v.e;
                 r.h = 0u;
-                store_global(left + n, r);
+                if (J.lng) shared_store_as(both + n, r);
+                else Ls[n] = r;
             }
         }
         // (no partner: the padded subtree adds +0, the node is this subtree)
         l += 1u;
         i >>= 1;
     }
-    // root: pooled sums of the next epoch, then M, then publish
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    // root: pooled sums of the next epoch, then M, then publish.  (The last
+    // epoch's copy was written past the L2 to a fresh place, as this one's is.)
+    if (J.lng) writes_arrived();
     const SumRec* Gprev = (e == 0u) ? P.G : J.gver + (size_t)(e - 1u) * (row + JOB_GAP);
     SumRec* Gnext = J.gver + (size_t)e * (row + JOB_GAP);
     SumRec* Gctx = const_cast<SumRec*>(P.G);
+#pragma unroll 4
     for (uint32_t n = (uint32_t)lane; n < n1; n += 64u) {
         const SumRec a = load_global(Gprev + n);
-        const SumRec b = load_global(P.L + n);            // the root's row is leaf 0's
-        const XF v = xf_add(xf_of(a), xf_of(b));
+        const XF v = xf_add(xf_of(a), xf_of(own(n)));
         SumRec r;
         r.m = v.m;
         r.e = v.e;
         r.h = 0u;
-        store_global(Gnext + n, r);
-        store_global(Gctx + n, r);
+        shared_store_as(Gnext + n, r);
+        shared_store_as(Gctx + n, r);
     }
     // the stop rule's group sums: lane k < 16 folds group k (sequences k, k + 16,
     // ... in order) into the context's running group sum and tour count
@@ -1660,19 +1738,21 @@ __device__ void job_merge(const JobArgs& A, const JobProblem& J, const ProblemDe
         if ((uint32_t)lane < GROUPS) {
             XF acc = {0.0, 0};
             uint64_t t = 0;
+#pragma unroll 4
             for (uint32_t q = (uint32_t)lane; q < J.N; q += GROUPS) {
-                acc = xf_add(acc, xf_of(load_global(J.stage + q)));
-                t += J.stage_m[q];
+                const SumRec r = shared_load_as(J.stage + q);
+                acc = xf_add(acc, xf_of(r));
+                t += r.h;
             }
-            const XF g = xf_add(xf_of(load_global(J.gsum + lane)), acc);
+            const XF g = xf_add(xf_of(shared_load_as(J.gsum + lane)), acc);
             uint64_t* gtours = reinterpret_cast<uint64_t*>(J.gsum + GROUPS);
-            gt = gtours[lane] + t;
+            gt = shared_load(gtours + lane) + t;
             SumRec r;
             r.m = g.m;
             r.e = g.e;
             r.h = 0u;
-            store_global(J.gsum + lane, r);
-            gtours[lane] = gt;
+            shared_store_as(J.gsum + lane, r);
+            shared_store(gtours + lane, gt);
             gm = g.m;
             ge = g.e;
         }
@@ -1704,13 +1784,12 @@ __device__ void job_merge(const JobArgs& A, const JobProblem& J, const ProblemDe
             rel = __builtin_sqrt(ss / (GROUPS - 1)) / (4.0 * mean);
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (lane == 0) {
-        const uint32_t msum = __hip_atomic_exchange(&A.state[pi].msum, 0u, __ATOMIC_ACQ_REL,
+        const uint32_t msum = __hip_atomic_exchange(&A.state[pi].msum, 0u, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
         uint64_t* MG = const_cast<uint64_t*>(P.MG);
-        const uint64_t M = MG[0] + msum;
-        MG[0] = M;
+        const uint64_t M = shared_load(MG) + msum;
+        shared_store(MG, M);
         // a problem one of whose sequences hit its step cap stops after this
         // epoch (its context reports the overflow); the others run on
         const bool failed =
@@ -1721,17 +1800,17 @@ __device__ void job_merge(const JobArgs& A, const JobProblem& J, const ProblemDe
         else if (J.cap != 0u && M >= J.cap) stop = STOP_CAP;
         if (failed) __hip_atomic_fetch_add(&A.counters[JOB_FAILED], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (J.result != nullptr) {
-            J.result[0] = e + 1u;
-            J.result[1] = stop;
-            J.result[2] = (uint32_t)__double2loint(rel);
-            J.result[3] = (uint32_t)__double2hiint(rel);
+            shared_store(J.result + 0, e + 1u);
+            shared_store(J.result + 1, stop);
+            shared_store(J.result + 2, (uint32_t)__double2loint(rel));
+            shared_store(J.result + 3, (uint32_t)__double2hiint(rel));
         }
         const bool last = stop != 0u || e + 1u == J.epochs;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        writes_arrived();
         __hip_atomic_store(&A.state[pi].word, (unsigned long long)(last ? J.epochs : e + 1u) << 32,
-                           __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (last)
-            __hip_atomic_fetch_add(&A.counters[JOB_FINISHED0 + J.cls], 1u, __ATOMIC_RELEASE,
+            __hip_atomic_fetch_add(&A.counters[JOB_FINISHED0 + J.cls], 1u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -1743,6 +1822,7 @@ __global__ void WAVES4 job_kernel(JobArgs A) {
     const int lane = (int)threadIdx.x;
     uint64_t idle_since = __builtin_amdgcn_s_memrealtime();
     uint32_t seen_progress = 0u;
+    uint32_t naps = 1u;
     // the slice's clock starts with the first wave to look at it
     unsigned long long* clock0 = reinterpret_cast<unsigned long long*>(A.counters + JOB_CLOCK);
     uint64_t start = 0;
@@ -1811,9 +1891,15 @@ __global__ void WAVES4 job_kernel(JobArgs A) {
                     __hip_atomic_fetch_add(&A.counters[JOB_BACKSTOP], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }
-            __builtin_amdgcn_s_sleep(127);
+            // (thousands of waves may be waiting, each poll reads a line per
+            // problem past the L2, and the working waves' claims and merges
+            // queue behind them: a wave that keeps finding nothing looks again
+            // after 3, 7, 14, 27 and at most 54 us)
+            for (uint32_t i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(127);
+            naps = min(2u * naps, 16u);
             continue;
         }
+        naps = 1u;
         // ---- the item: the sequence's tours of this epoch, then its merge part ----
         const JobProblem J = load_const(A.probs + pi);
         const ProblemDesc P = load_const(J.desc);
@@ -1827,14 +1913,18 @@ __global__ void WAVES4 job_kernel(JobArgs A) {
         const uint32_t cap = cap64 > (1ull << 31) ? (1u << 31) : (uint32_t)cap64;
         const SumRec* Gsrc = (e == 0u) ? P.G : J.gver + (size_t)(e - 1u) * (P.row + JOB_GAP);
         uint32_t rv;
-        if (J.lng)
-            rv = (P.dim == 2) ? walk_sequence<2, false, true>(J.desc, tours, cap, s, lds, Gsrc, true)
-                 : P.ckey     ? walk_sequence<3, false, true, true>(J.desc, tours, cap, s, lds, Gsrc, true)
-                              : walk_sequence<3, false, true>(J.desc, tours, cap, s, lds, Gsrc, true);
-        else
-            rv = (P.dim == 2) ? walk_sequence<2>(J.desc, tours, cap, s, lds, Gsrc, true)
-                 : P.ckey     ? walk_sequence<3, false, false, true>(J.desc, tours, cap, s, lds, Gsrc, true)
-                              : walk_sequence<3>(J.desc, tours, cap, s, lds, Gsrc, true);
+        if (J.lng) {
+            // (a long walk's row is read and written in place through the L2 of
+            // its XCD: what another one wrote there last must not be met)
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            rv = (P.dim == 2) ? walk_sequence<2, false, true, false, true>(J.desc, tours, cap, s, lds, Gsrc)
+                 : P.ckey     ? walk_sequence<3, false, true, true, true>(J.desc, tours, cap, s, lds, Gsrc)
+                              : walk_sequence<3, false, true, false, true>(J.desc, tours, cap, s, lds, Gsrc);
+        } else {
+            rv = (P.dim == 2) ? walk_sequence<2, false, false, false, true>(J.desc, tours, cap, s, lds, Gsrc)
+                 : P.ckey     ? walk_sequence<3, false, false, true, true>(J.desc, tours, cap, s, lds, Gsrc)
+                              : walk_sequence<3, false, false, false, true>(J.desc, tours, cap, s, lds, Gsrc);
+        }
         if ((rv & WALK_ABORTED) && lane == 0)
             __hip_atomic_fetch_or(&A.state[pi].failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         job_merge(A, J, P, pi, e, s, rv & ~WALK_ABORTED, lds);
