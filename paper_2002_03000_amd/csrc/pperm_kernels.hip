@@ -764,16 +764,22 @@ template <int D, bool CK> struct SiteOf { using T = Site2; };
 template <> struct SiteOf<3, false> { using T = Site3; };
 template <> struct SiteOf<3, true> { using T = Site3c; };
 
-// Set bits of m, counted on the vector side: a lane mask that a vector compare
-// wrote costs the scalar unit a wait of some 16 cycles before it can read it.
-// (The two wait states are the hardware's between a vector instruction that
-// writes a scalar register and one that reads it.)
-__device__ __forceinline__ uint32_t mask_count(uint64_t m) {
+// Set bits of m, counted on the vector side (a lane mask that a vector compare
+// wrote costs the scalar unit a wait of some 16 cycles before it can read it),
+// and x * 2^e beside it: the two instructions between the compare and the counts
+// are the wait states the hardware wants between a vector instruction that
+// writes a scalar register and one that reads it.
+__device__ __forceinline__ uint32_t mask_count(uint64_t m, double x, int e, int scale, double& scaled) {
     uint32_t r;
-    asm("s_nop 1\n\t"
-        "v_bcnt_u32_b32 %0, %1, 0\n\t"
-        "v_bcnt_u32_b32 %0, %2, %0"
-        : "=&v"(r) : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)));
+    int d;
+    double y;
+    asm("v_sub_u32 %1, %6, %7\n\t"
+        "v_ldexp_f64 %2, %5, %1\n\t"
+        "v_bcnt_u32_b32 %0, %3, 0\n\t"
+        "v_bcnt_u32_b32 %0, %4, %0"
+        : "=&v"(r), "=&v"(d), "=&v"(y)
+        : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)), "v"(x), "v"(e), "v"(scale));
+    scaled = y;
     return r;
 }
 
@@ -795,6 +801,10 @@ template <typename T>
 __device__ __forceinline__ T lds_load(uint32_t address) {
     return *(const __attribute__((address_space(3))) T*)(uintptr_t)address;
 }
+template <typename T>
+__device__ __forceinline__ void lds_store(uint32_t address, T v) {
+    *(__attribute__((address_space(3))) T*)(uintptr_t)address = v;
+}
 // A record read whole through a word vector.
 __device__ __forceinline__ SumRec record_of(u32x4 w) {
     SumRec r;
@@ -813,52 +823,43 @@ __device__ __forceinline__ u32x4 words_of(double m, int32_t e, uint32_t h) {
     return r;
 }
 
-// One arrival's writes, by lane `il` alone: the site's key into its table slot,
-// its slot id, and the record of its length (in LDS, or with LONG in global
-// memory).  taddr: the slot's LDS address in lane il; saddr, raddr: the slot-id
-// and record addresses of the length before.  One lane selected with a scalar
-// shift takes two instructions; a compare and a saved mask would take six.
-template <bool LONG>
+// One arrival's writes to LDS, by lane `il` alone: the site's key into its table
+// slot, its slot id, and the record of its length (for long walks the record goes
+// to global memory, see there).  taddr: the slot's LDS address in lane il; saddr,
+// raddr: the addresses of the length's slot id and record.  One lane selected
+// with a scalar shift takes two instructions; a compare and a saved mask would
+// take six and a wait.
 __device__ __forceinline__ void write_arrival(uint32_t il, uint32_t taddr, uint32_t key, uint32_t saddr,
-                                              uint32_t slot, uint32_t raddr, u32x4 rec, const void* gbase) {
-    if constexpr (LONG)
-        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
-                     "ds_write_b32 %1, %2\n\t"
-                     "ds_write_b16 %3, %4 offset:2\n\t"
-                     "s_nop 1\n\t"
-                     "global_store_dwordx4 %5, %6, %7 offset:16\n\t"
-                     "s_mov_b64 exec, -1"
-                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec), "s"(gbase)
-                     : "memory", "scc");
-    else
-        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
-                     "ds_write_b32 %1, %2\n\t"
-                     "ds_write_b16 %3, %4 offset:2\n\t"
-                     "ds_write_b128 %5, %6 offset:16\n\t"
-                     "s_mov_b64 exec, -1"
-                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec)
-                     : "memory", "scc");
+                                              uint32_t slot, uint32_t raddr, u32x4 rec) {
+    asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                 "ds_write_b32 %1, %2\n\t"
+                 "ds_write_b16 %3, %4\n\t"
+                 "ds_write_b128 %5, %6\n\t"
+                 "s_mov_b64 exec, -1"
+                 :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec) : "memory", "scc");
 }
-template <bool LONG>
 __device__ __forceinline__ void write_arrival(uint32_t il, uint32_t taddr, uint64_t key, uint32_t saddr,
-                                              uint32_t slot, uint32_t raddr, u32x4 rec, const void* gbase) {
-    if constexpr (LONG)
-        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
-                     "ds_write_b64 %1, %2\n\t"
-                     "ds_write_b16 %3, %4 offset:2\n\t"
-                     "s_nop 1\n\t"
-                     "global_store_dwordx4 %5, %6, %7 offset:16\n\t"
-                     "s_mov_b64 exec, -1"
-                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec), "s"(gbase)
-                     : "memory", "scc");
-    else
-        asm volatile("s_lshl_b64 exec, 1, %0\n\t"
-                     "ds_write_b64 %1, %2\n\t"
-                     "ds_write_b16 %3, %4 offset:2\n\t"
-                     "ds_write_b128 %5, %6 offset:16\n\t"
-                     "s_mov_b64 exec, -1"
-                     :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec)
-                     : "memory", "scc");
+                                              uint32_t slot, uint32_t raddr, u32x4 rec) {
+    asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                 "ds_write_b64 %1, %2\n\t"
+                 "ds_write_b16 %3, %4\n\t"
+                 "ds_write_b128 %5, %6\n\t"
+                 "s_mov_b64 exec, -1"
+                 :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot), "v"(raddr), "v"(rec) : "memory", "scc");
+}
+__device__ __forceinline__ void write_site(uint32_t il, uint32_t taddr, uint32_t key, uint32_t saddr, uint32_t slot) {
+    asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                 "ds_write_b32 %1, %2\n\t"
+                 "ds_write_b16 %3, %4\n\t"
+                 "s_mov_b64 exec, -1"
+                 :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot) : "memory", "scc");
+}
+__device__ __forceinline__ void write_site(uint32_t il, uint32_t taddr, uint64_t key, uint32_t saddr, uint32_t slot) {
+    asm volatile("s_lshl_b64 exec, 1, %0\n\t"
+                 "ds_write_b64 %1, %2\n\t"
+                 "ds_write_b16 %3, %4\n\t"
+                 "s_mov_b64 exec, -1"
+                 :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot) : "memory", "scc");
 }
 
 // The lowest bit set in m, or all ones for none.
@@ -886,6 +887,63 @@ __device__ __forceinline__ void clear_sites(uint32_t index, uint32_t depth, uint
                      :: "v"(index), "v"(depth), "v"(at), "v"(zero) : "memory", "vcc");
 }
 
+// The copy stack's registers: one pending entry per lane.
+template <typename Key>
+struct CopyLanes {
+    uint32_t ra, rem;      // the length (its record's address) and the copies to resume
+    int32_t e;             // their weight m * 2^e
+    double m;
+    Key key;               // the walk's end
+};
+
+// Writes lane p mod 64 of the entries, selected with a scalar shift.
+template <typename Key>
+__device__ __forceinline__ void put_entry(CopyLanes<Key>& c, uint32_t p, uint32_t ra, uint32_t rem, int32_t e,
+                                          double m, Key key) {
+    const uint64_t mb = __builtin_bit_cast(uint64_t, m);
+    uint64_t cm = __builtin_bit_cast(uint64_t, c.m);
+    uint32_t mlo = (uint32_t)cm, mhi = (uint32_t)(cm >> 32);
+    if constexpr (sizeof(Key) == 8) {
+        uint32_t klo = (uint32_t)c.key, khi = (uint32_t)(c.key >> 32);
+        asm volatile("s_lshl_b64 exec, 1, %7\n\t"
+                     "v_mov_b32 %0, %8\n\t"
+                     "v_mov_b32 %1, %9\n\t"
+                     "v_mov_b32 %2, %10\n\t"
+                     "v_mov_b32 %3, %11\n\t"
+                     "v_mov_b32 %4, %12\n\t"
+                     "v_mov_b32 %5, %13\n\t"
+                     "v_mov_b32 %6, %14\n\t"
+                     "s_mov_b64 exec, -1"
+                     : "+v"(c.ra), "+v"(c.rem), "+v"(c.e), "+v"(mlo), "+v"(mhi), "+v"(klo), "+v"(khi)
+                     : "s"(p), "v"(ra), "v"(rem), "v"(e), "v"((uint32_t)mb), "v"((uint32_t)(mb >> 32)),
+                       "v"((uint32_t)key), "v"((uint32_t)(key >> 32))
+                     : "scc");
+        c.key = ((uint64_t)khi << 32) | klo;
+    } else {
+        asm volatile("s_lshl_b64 exec, 1, %6\n\t"
+                     "v_mov_b32 %0, %7\n\t"
+                     "v_mov_b32 %1, %8\n\t"
+                     "v_mov_b32 %2, %9\n\t"
+                     "v_mov_b32 %3, %10\n\t"
+                     "v_mov_b32 %4, %11\n\t"
+                     "v_mov_b32 %5, %12\n\t"
+                     "s_mov_b64 exec, -1"
+                     : "+v"(c.ra), "+v"(c.rem), "+v"(c.e), "+v"(mlo), "+v"(mhi), "+v"(c.key)
+                     : "s"(p), "v"(ra), "v"(rem), "v"(e), "v"((uint32_t)mb), "v"((uint32_t)(mb >> 32)), "v"(key)
+                     : "scc");
+    }
+    c.m = __builtin_bit_cast(double, ((uint64_t)mhi << 32) | mlo);
+}
+
+// One copy less to resume in lane p mod 64.
+template <typename Key>
+__device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
+    asm volatile("s_lshl_b64 exec, 1, %1\n\t"
+                 "v_add_u32 %0, -1, %0\n\t"
+                 "s_mov_b64 exec, -1"
+                 : "+v"(c.rem) : "s"(p) : "scc");
+}
+
 // One sequence's `tours` tours against frozen pooled sums (the whole hot path
 // of one walk); run by one wavefront.  Gsrc: the pooled sums to read (the
 // problem's own, or an epoch's copy in a chained launch).  Returns the tours
@@ -905,23 +963,29 @@ __device__ __forceinline__ void clear_sites(uint32_t index, uint32_t depth, uint
 // for a branch not taken, 20 for one taken, 16 where the scalar unit reads what
 // the vector unit wrote.  So the common event -- a walk with a free neighbour,
 // a decision that keeps one copy (or a survivor), a growth that ends neither
-// the walk, the random block nor the step budget -- is one straight block of 78
+// the walk, the random block nor the step budget -- is one straight block of 71
 // instructions, mostly vector code, with a single branch, its own loop's
 // (run_ahead); enrichment to two copies, pruning and trapping (a quarter of the
 // square lattice's events) are short blocks beside it; and everything else is
 // handled outside, in the extended-range form (the event loop).
 // Measured (ms): with every case decided in line, 255 instructions and 17
-// branches a step / the straight block alone / with the blocks beside it:
-//   one square sequence of 20-step walks, 1000 tours       12.46 / 8.42 / 6.72
-//   4096 square sequences of 500 steps, 64 tours            94.6 / 70.2 / 47.6
-//   16384 cubic sequences of 1000 steps, 32 tours            198 /  149 /  101
-//   256 Rosenbluth walks of up to 6000 cubic steps, twice   6.41 / 3.40 / 2.15
+// branches a step / the straight block alone, 87 instructions / 78, with the
+// blocks beside it / 71, with the scalar unit's waits filled and every value of
+// the walk that is the same in all lanes known to be so:
+//   one square sequence of 20-step walks, 1000 tours       12.46 / 8.42 / 6.72 / 6.48
+//   4096 square sequences of 500 steps, 64 tours            94.6 / 70.2 / 47.6 / 46.5
+//   16384 cubic sequences of 1000 steps, 32 tours            198 /  149 /  101 / 98.9
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice   6.41 / 3.40 / 2.15 / 1.97
+// A lone wave's step (us): square 0.625 -> 0.267, cubic 0.610 -> 0.259.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 
 template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false>
 __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint32_t tours, uint32_t cap,
                                                   uint32_t s, unsigned char* lds, const SumRec* Gsrc) {
     static_assert(!(OBS && JOB), "chained launches keep no observables");
+    // (loads through a generic pointer pass for lane values)
+    tours = ufirst(tours);
+    cap = ufirst(cap);
     const ProblemDesc P = load_const(desc);
     static_assert(!(OBS && CK), "observables need coordinates, which compact keys do not keep");
     using S_ = typename SiteOf<D, CK>::T;
@@ -975,7 +1039,17 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     const uint32_t lane_base = blank ? S - 1u : (uint32_t)poff * sub;
     const uint32_t lane_mul = ((0x9E3779B1u * (uint32_t)(poff + 1)) ^ (0x85EBCA77u * (uint32_t)(poff + 3))) | 1u;
     const Key pdelta = S_::delta(pdir);
-    auto slot_of = [&](Key k) INLINE { return __umulhi(S_::word(k) * lane_mul, lane_sub) + lane_base; };
+    // (as an LDS address)
+    uint32_t lane_at = lane_base * (uint32_t)sizeof(Key) + lds_address(table);
+    asm volatile("" : "+v"(lane_at));          // (one addend)
+    auto place_of = [&](Key k) INLINE {
+        uint32_t h = __umulhi(S_::word(k) * lane_mul, lane_sub);
+        asm("" : "+v"(h));                     // (or the shift is merged into the 64-bit product)
+        return h * (uint32_t)sizeof(Key) + lane_at;
+    };
+    // a site's slot id: its LDS address in keys (16 bits: LDS has 160 KB)
+    auto id_of = [&](uint32_t place) INLINE { return place / (uint32_t)sizeof(Key); };
+    auto clear_id = [&](uint32_t i) INLINE { lds_store<Key>(i * (uint32_t)sizeof(Key), (Key)0); };
 
     // A zero the compiler cannot see through: addresses and sums formed with it
     // stay in vector registers.
@@ -994,9 +1068,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     wave_fence();
     const Key origin_key = S_::origin();
     if (lane == 0) {                           // (lane 0: subtable 0)
-        const uint32_t o = slot_of(origin_key);
-        table[o] = origin_key;
-        sid[0] = (uint16_t)o;
+        const uint32_t o = place_of(origin_key);
+        lds_store<Key>(o, origin_key);
+        sid[0] = (uint16_t)id_of(o);
     }
     wave_fence();
 
@@ -1030,10 +1104,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     uint32_t digest = (uint32_t)(JOB ? shared_load(old_digest) : *old_digest) + vz;
     bool abort = false;
     // the registers of the copy stack (see the tour loop)
-    uint32_t cs_ra = 0u, cs_rem = 0u;
-    int32_t cs_e = 0;
-    double cs_m = 0.0;
-    Key cs_key = (Key)0;
+    CopyLanes<Key> cs = {0u, 0u, 0, 0.0, (Key)0};
 
     // byte addresses of length 0: its record (in LDS, or with LONG as an offset
     // from the row) and its slot id; gsums + a record's address is the pooled
@@ -1041,10 +1112,17 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     const uint32_t rec_base = LONG ? 0u : lds_address(Ls);
     const uint32_t sid_base = lds_address(sid);
     const unsigned char* gsums = reinterpret_cast<const unsigned char*>(Grow) - rec_base;
-    auto pooled = [&](uint32_t address) INLINE {
-        return load_global(reinterpret_cast<const SumRec*>(gsums + address));
+    auto pooled = [&](uint32_t address, uint32_t ahead) INLINE {
+        return load_global(reinterpret_cast<const SumRec*>(gsums + ahead * 16u + address));
     };
 
+    // (LONG) the row as a buffer: lane 0 stores a record, the other lanes' offsets
+    // are past its end and dropped.  (A store among inline assembly would not be
+    // counted by the compiler, which then waits for it where it waits for the
+    // loads before it: 0.35 us a step instead of 0.28.)
+    const __amdgpu_buffer_rsrc_t row_out =
+        __builtin_amdgcn_make_buffer_rsrc(Ls, 0, (int)(row * (uint32_t)sizeof(SumRec)), 0x00020000);
+    const uint32_t lane_out = lane == 0 ? 0u : 0x80000000u;
     // 2^-501 in a register (see run_ahead), and twice the lane
     double small = 0x1p-501;
     asm volatile("" : "+v"(small));
@@ -1086,7 +1164,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         Key ekey = origin_key;                 // the walk's end
         uint32_t far_lo = ~0u;                 // first site of the walk outside its places
         // pending copies: sp entries, the one at position p in lane p mod 64
-        // of the cs_* registers for p >= lo, in global memory for p < lo (at
+        // of cs for p >= lo, in global memory for p < lo (at
         // most 64 in registers; the most recent ones, which are resumed first)
         uint32_t sp = 0, lo = 0;
         // tours seen by the running average of eqn (6) (reading of Algorithm 2)
@@ -1096,30 +1174,30 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         const double seen_r = recip_normal(seen);
 
         // The walk's weight wm * 2^we, its sum at this length Lm * 2^we and the
-        // pooled sum Gm * 2^Ge.  Inside run_ahead mantissas are left as they
+        // pooled sum G (the next length's once scan has used it).  Inside run_ahead mantissas are left as they
         // come (a power-of-two scale commutes with every rounding as long as
         // nothing leaves the FP64 range) and we is constant, so a sum costs one
         // exact shift of the other operand and the ratio none.  wm is in
         // [0.5, 1) when a block of events begins or a copy resumes; one event
         // at most halves it or makes it 2^6.6 times larger.
-        double wm, Lm, Gm;
-        int we, Ge;
+        double wm, Lm;
+        int we;
+        SumRec G;
         double uf = 0.0;                       // what run_ahead compares (see arm)
-        uint32_t last = 0;                     // the event that stops it whatever it is
         SumRec nxt = {0.0, 0, 0u}, nxr = {0.0, 0, 0u};   // records of the next length
         auto steps = [&]() INLINE { return (uint32_t)c_events + kb + li - 1u - c_prunes; };
         // Makes the next events ready for run_ahead: lane i of uf holds the
         // uniform of its event, but at least 1/16 (survival at a ratio below
         // that, which could scale wm without limit, is decided outside, as is a
-        // uniform of 0), and 2 (never below a threshold) from the event on that
-        // could end the walk or the step budget, or at once while some site is
+        // uniform of 0), and no number (which fails every test) from the event
+        // on that could end the walk or the step budget, or at once while some site is
         // outside its places.  (After a resume the walk's end is further off
         // than this says, which only stops run_ahead for nothing.)
         auto arm = [&](uint32_t n) INLINE {
             const uint32_t left = min(n_max - n, capv - steps());
-            last = far_lo != ~0u ? li : min(64u, li + left - 1u);
+            const uint32_t last = far_lo != ~0u ? li : li + left - 1u;
             const double uu = u < 0.0625 ? 0.0625 : u;
-            uf = ((uint32_t)lane >= last || lane == 0) ? 2.0 : uu;
+            uf = ((uint32_t)lane >= last || lane == 0) ? __builtin_nan("") : uu;
         };
         // (LONG) the next length's records, from global memory
         auto load_next = [&]() INLINE {
@@ -1135,8 +1213,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         // 1, which keeps one copy (and no sum, Lm = 0, marks the case).
         auto no_decision = [&]() INLINE {
             Lm = 0.0;
-            Gm = wm * seen;
-            Ge = we;
+            G.m = wm * seen;
+            G.e = we;
         };
         auto weigh = [&](XF w) INLINE {
             wm = w.m;
@@ -1151,15 +1229,15 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         // what scan leaves: the neighbours' keys, slots and contents, the hits,
         // a_+, the choice, and the decision
         Key nk, v;
-        uint32_t slot, a, x, il;
-        uint64_t hits, pick;
-        double t, ut, uu, r = 0.0, w1;
-        SumRec Gn, nx2 = {0.0, 0, 0u}, nr2 = {0.0, 0, 0u};
+        uint32_t place, a, x, il, a8, id, hn;
+        uint64_t hits, pick, choice, below1 = 0ull;
+        double t, ut, uu, r = 0.0, w1, af;
+        SumRec nx2 = {0.0, 0, 0u}, nr2 = {0.0, 0, 0u};
         auto scan = [&](auto decide) INLINE {
             // occupancy reads, the next length's record and pooled sum
             nk = S_::next(ekey, pdelta);
-            slot = slot_of(nk);
-            v = lds_load<Key>(slot * (uint32_t)sizeof(Key) + lds_address(table));
+            place = place_of(nk);
+            v = lds_load<Key>(place);
             if constexpr (LONG) {
                 // (one length further: it has a whole step to arrive.  At
                 // n_max - 1 that is past the last record: row is padded to
@@ -1180,16 +1258,18 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 // data weighted N in Algorithm 2), as (W * seen) / sum.
                 // One copy goes on iff u < r < 1 (a survivor, which takes
                 // sum / seen) or 1 <= r < 2 and u < 2 - r.
-                const double sum = ldexp(Gm, Ge - we) + Lm * pool;
+                const double sum = ldexp(G.m, G.e - we) + Lm * pool;
                 r = div_by(wm * seen, sum, recip_normal(sum));
                 thr = min_f64(r, 2.0 - r);
                 const double ws = div_by(sum, seen, seen_r);
+                below1 = __ballot(r < 1.0);
                 w1 = r < 1.0 ? ws : wm;
-                Gn = pooled(ra + 16u);
+                G = pooled(ra, 1u);
             }
             __builtin_amdgcn_sched_barrier(0);
             hits = __ballot(v == nk);
-            a = (uint32_t)(2 * D) - mask_count(hits);
+            // (and the next length's sum at this scale)
+            a = (uint32_t)(2 * D) - mask_count(hits, nxt.m, nxt.e, we, t);
             // The j-th free neighbour, j = floor(B0 a / 2^32): the number
             // of free directions below a lane's own is pdir less the hits
             // in lanes below it, so x is 0 in the chosen direction's
@@ -1201,22 +1281,39 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
                                           __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j - (uint32_t)pdir));
             pick = __ballot((x | S_::mark(v)) == 0u);
-            // the next length's sum at this scale; the term that adds it
-            // to u is below its last place unless the sum is 2^440 times
-            // the weight or more, which stops here
-            t = ldexp(nxt.m, nxt.e - we);
+            // (the term that adds the next sum to u is below u's last place
+            // unless the sum is 2^440 times the weight or more, which stops here)
             ut = __builtin_fma(t, small, uu);
-            il = first_bit(pick & __ballot(ut < thr));
+            const uint64_t ok = __ballot(ut < thr);
+            __builtin_amdgcn_sched_barrier(0);
+            // what growth needs whoever is chosen, while the scalar unit waits
+            af = (double)a;
+            a8 = a << 3;
+            id = id_of(place);
+            hn = nxt.h + 1u;
+            asm volatile("" : "+v"(af), "+v"(a8), "+v"(id), "+v"(hn));
+            __builtin_amdgcn_sched_barrier(0);
+            choice = pick & ok;
+            il = first_bit(choice);
         };
         // (il is all ones where nothing was chosen, and a last lane where all
         // places of the chosen neighbour are taken)
         auto chosen = [&]() INLINE { return (~il & (uint32_t)(W - 1)) != 0u; };
         // growth by the lane `il`: W *= a_+, eqn (2), and the record, eqn (4)
         auto commit = [&](double w) INLINE {
-            wm = w * (double)a;
+            wm = w * af;
             Lm = t + wm;
-            write_arrival<LONG>(il, slot * (uint32_t)sizeof(Key) + lds_address(table), nk, sa, slot, ra,
-                                words_of(Lm, we, nxt.h + 1u), Ls);
+            ra += 16u;
+            asm volatile("" : "+v"(ra));       // (in place, not beside the old value)
+            sa += 2u;
+            li += 1u;
+            const u32x4 rec = words_of(Lm, we, hn);
+            if constexpr (LONG) {
+                write_site(il, place, nk, sa, id);
+                __builtin_amdgcn_raw_buffer_store_b128(rec, row_out, ra | lane_out, 0, 0);
+            } else {
+                write_arrival(il, place, nk, sa, id, ra, rec);
+            }
             ekey = lane_value(nk, il);
             if constexpr (OBS) {
                 // R^2 of the new end, exact in FP64 (|coordinates| < 2^15)
@@ -1229,17 +1326,12 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 rr.h = 0u;
                 if (lane == 0) {
                     if constexpr (LONG)
-                        store_global(reinterpret_cast<SumRec*>(reinterpret_cast<unsigned char*>(LRs) + ra) + 1, rr);
+                        store_global(reinterpret_cast<SumRec*>(reinterpret_cast<unsigned char*>(LRs) + ra), rr);
                     else
-                        *reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds + (ra - rec_base) + 16u) = rr;
+                        *reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds + (ra - rec_base)) = rr;
                 }
             }
-            digest = (digest ^ ((il >> LW) | (a << 3))) * FNV_PRIME;
-            Gm = Gn.m;
-            Ge = Gn.e;
-            ra += 16u;
-            sa += 2u;
-            li += 1u;
+            digest = (digest ^ ((il >> LW) | a8)) * FNV_PRIME;
             if constexpr (LONG) {
                 nxt = nx2;
                 if constexpr (OBS) nxr = nr2;
@@ -1247,77 +1339,86 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         };
         // a copy stack entry: `copies` still to resume here with weight w
         auto push = [&](double w, uint32_t copies) INLINE {
-            const bool mine = lane == (int)(sp & 63u);
-            cs_ra = mine ? ra : cs_ra;
-            cs_rem = mine ? copies : cs_rem;
-            cs_e = mine ? we : cs_e;
-            cs_m = mine ? w : cs_m;
-            cs_key = mine ? ekey : cs_key;
+            put_entry(cs, sp, ra, copies + vz, we, w, ekey);
             sp += 1u;
             c_maxd = max(c_maxd, sp);
             c_enrich += 1u;
             c_copies += (uint64_t)copies;
         };
         // back to the most recent pending copy, which the registers hold
-        auto resume = [&]() INLINE {
-            // (the slot ids of the last 64 sites; a short walk's reach into the
-            // table before them and are not used)
-            uint32_t at = lds_load<uint16_t>(sa - lane2);
+        // (at: the slot ids of the last 64 sites; a short walk's reach into the
+        // table before them and are not used)
+        auto last_ids = [&]() INLINE { return (uint32_t)lds_load<uint16_t>(sa - lane2); };
+        auto resume = [&](uint32_t at) INLINE {
             const uint32_t tl = (sp - 1u) & 63u;
-            const uint32_t rem = lane_value(cs_rem, tl);
-            const double wv = lane_value(cs_m, tl);
+            const double wv = lane_value(cs.m, tl);
             wm = __builtin_amdgcn_frexp_mant(wv);
-            we = (int)lane_value((uint32_t)cs_e, tl) + __builtin_amdgcn_frexp_exp(wv) + (int)vz;
+            we = (int)lane_value((uint32_t)cs.e, tl) + __builtin_amdgcn_frexp_exp(wv) + (int)vz;
             asm volatile("" : "+v"(wm));
-            ekey = lane_value(cs_key, tl);
-            ra = lane_value(cs_ra, tl) + vz;
-            if (rem == 1u) sp -= 1u;           // its last copy: the entry is done
-            cs_rem -= (lane == (int)tl) ? 1u : 0u;
+            ekey = lane_value(cs.key, tl);
+            ra = lane_value(cs.ra, tl) + vz;
+            const uint32_t rem = lane_value(cs.rem, tl);
+            take_copy(cs, tl);
             // LIFO deletion of the sites after it restores the table exactly
-            const uint32_t back = (ra >> 3) + (sid_base - rec_base / 8u);
-            clear_sites<Key>(lane2, sa - back, at * (uint32_t)sizeof(Key) + lds_address(table));
-            for (uint32_t d = 128u; __ballot(sa - back > d) != 0ull; d += 128u)
-                if (lane2 + d < sa - back)
-                    table[*(const __attribute__((address_space(3))) uint16_t*)(uintptr_t)(sa - d - lane2)] = (Key)0;
-            sa = back;
+            const uint32_t end = sa;
+            sa = (ra >> 3) + (sid_base - rec_base / 8u);
+            clear_sites<Key>(lane2, end - sa, at * (uint32_t)sizeof(Key));
+            for (uint32_t d = 128u; __ballot(end - sa > d) != 0ull; d += 128u) {
+                at = lds_load<uint16_t>(end - d - lane2);
+                clear_sites<Key>(lane2 + d, end - sa, at * (uint32_t)sizeof(Key));
+            }
+            sp -= rem == 1u ? 1u : 0u;         // its last copy: the entry is done
             no_decision();
             load_next();
         };
         // Runs common events, the enrichments that make two copies and the
         // prunings, until an event needs more: false, the event at li is still
         // to be handled; true, a copy ended and no pending one is in registers.
+        // (No variable is declared inside its loop, and all its ways out are
+        // one: blocks that only tell them apart would each copy everything a
+        // step changes.)
+        uint32_t pruned, ended, at;
         auto run_ahead = [&](auto decide) INLINE -> bool {
+            ended = 0u;
             for (;;) {
                 scan(decide);
                 while (chosen()) {
                     commit(w1);
                     scan(decide);
                 }
-                if (li >= last) return false;
-                uint32_t pruned = 0u;          // or no free neighbour: a trap, no event
-                if (pick != 0ull) {
-                    if constexpr (decltype(decide)::value) {
-                        // (uu is the uniform itself where 1/16 or more is compared)
-                        if (__ballot(r < 1.0 && r >= 0.0625 && uu >= r) == 0ull) {
-                            // 1 <= r < 2 and u >= 2 - r: two copies
-                            if (__ballot(r >= 1.0 && r <= 1.9375 && ut == uu) == 0ull) return false;
-                            il = first_bit(pick);
-                            if (!chosen() || sp - lo == 64u) return false;
-                            push(0.5 * wm, 1u);
-                            commit(0.5 * wm);
-                            continue;
-                        }
-                        pruned = 1u;           // r < 1, pruned with probability 1 - r
-                    } else {
-                        return false;
+                if constexpr (decltype(decide)::value) {
+                    // (a ratio out of range, a uniform that is not the event's or
+                    // a sum out of range: no number passes)
+                    at = last_ids();           // (for resume, while the tests wait)
+                    if ((__ballot(r > 0.0625) & __ballot(r < 1.9375) & __ballot(ut == uu)) == 0ull) break;
+                    if (choice != 0ull) break; // the decision was common: all places taken
+                    if (below1 == 0ull) {
+                        // 1 <= r < 2 and u >= 2 - r: two copies
+                        il = first_bit(pick);
+                        if (!chosen()) break;  // (no free neighbour, or no free place)
+                        if (sp - lo == 64u) break;
+                        push(0.5 * wm, 1u);
+                        commit(0.5 * wm);
+                        continue;
                     }
+                    // u >= r, pruned with probability 1 - r, unless no neighbour
+                    // is free: a trap, and no event
+                    pruned = pick != 0ull ? 1u : 0u;
+                } else {
+                    if (pick != 0ull || li == 64u) break;
+                    at = last_ids();
+                    pruned = 0u;
                 }
                 c_prunes += pruned;
                 c_traps += 1u - pruned;
                 li += pruned;
-                if (sp == lo) return true;
-                resume();
+                if (sp == lo) {
+                    ended = 1u;
+                    break;
+                }
+                resume(at);
             }
+            return ufirst(ended) != 0u;
         };
 
         for (;;) {
@@ -1330,6 +1431,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 const XF w = xf_norm_nz(wm, we);
                 Lm = ldexp(Lm, we - w.e);
                 weigh(w);
+                // (scan has moved on to the next length's sum)
+                if (__ballot(Lm != 0.0) != 0ull) G = pooled(ra, 0u);
+                else no_decision();
                 arm(length());
                 continue;
             }
@@ -1340,7 +1444,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 if (far_lo != ~0u) {
                     for (uint32_t b = far_lo; b <= n; b += 64u) {
                         const uint32_t i = b + (uint32_t)lane;
-                        const Key k = i <= n ? table[sid[i]] : (Key)0;
+                        const Key k = i <= n ? lds_load<Key>(sid[i] * (uint32_t)sizeof(Key)) : (Key)0;
                         for (int d = 0; d < 2 * D; ++d)
                             if (__ballot(k == lane_value(nk, (uint32_t)(d * W))) != 0ull &&
                                 ((hits >> (d * W)) & FIELD) == 0ull)
@@ -1354,7 +1458,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     bt = true;
                 } else if (control_mode && __ballot(Lm != 0.0) != 0ull) {
                     const SumRec here = rec_ld(Ls + (n + vz));
-                    const XF sum = xf_add_nz(XF{Gm, Ge}, xf_mul_nz(xf_norm_nz(here.m, here.e), pool));
+                    const XF sum = xf_add_nz(xf_of(pooled(ra, 0u)), xf_mul_nz(xf_norm_nz(here.m, here.e), pool));
                     const double rr = xf_ratio_nz(xf_mul_nz(w, seen), sum);
                     const double ul = lane_value(u, li);
                     const double f = floor(rr);
@@ -1374,12 +1478,12 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                                 // to its place in global memory
                                 if (lane == (int)(lo & 63u)) {
                                     StackEntry e;
-                                    e.n = cs_ra;
-                                    e.remaining = cs_rem;
-                                    e.e = cs_e;
+                                    e.n = cs.ra;
+                                    e.remaining = cs.rem;
+                                    e.e = cs.e;
                                     e.pad0 = 0u;
-                                    e.m = cs_m;
-                                    e.key = (uint64_t)cs_key;
+                                    e.m = cs.m;
+                                    e.key = (uint64_t)cs.key;
                                     if constexpr (JOB) shared_store_as(stk + lo, e);
                                     else store_global(stk + lo, e);
                                 }
@@ -1404,7 +1508,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     }
                     il = (uint32_t)__builtin_ctzll(__ballot((x | S_::mark(v)) == 0u) & ~outside);
                     ekey = lane_value(nk, il);
-                    uint32_t ins = lane_value(slot, il);
+                    uint32_t ins = lane_value(place, il);
                     if (!chosen()) {
                         // all places taken: the first empty slot of the table
                         // (slots outnumber the sites of the longest walk)
@@ -1413,7 +1517,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                             const uint64_t em =
                                 __ballot(i < sub * (uint32_t)(W - 1) && S_::empty(table[min(i, S - 1u)]));
                             if (em != 0ull) {
-                                ins = b + (uint32_t)__builtin_ctzll(em);
+                                ins = lds_address(table + b + (uint32_t)__builtin_ctzll(em));
                                 break;
                             }
                         }
@@ -1431,8 +1535,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     nr.e = Lnew.e;
                     nr.h = nxt.h + 1u;
                     if (lane == 0) {
-                        table[ins] = ekey;
-                        sid[n] = (uint16_t)ins;
+                        lds_store<Key>(ins, ekey);
+                        sid[n] = (uint16_t)id_of(ins);
                         rec_st(Ls + n, nr);
                     }
                     if constexpr (OBS) {
@@ -1456,8 +1560,6 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     // number, and the decision comes here)
                     weigh(w);
                     Lm = ldexp(Lnew.m, Lnew.e - we);
-                    Gm = Gn.m;
-                    Ge = Gn.e;
                     load_next();
                     bt = n == n_max;
                 }
@@ -1469,20 +1571,21 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     // no pending entry in registers: bring back the most recent
                     // ones (up to 64) from global memory
                     const uint32_t base = sp > 64u ? sp - 64u : 0u;
-                    const uint32_t q = base + (((uint32_t)lane - base) & 63u);
-                    if (q < sp) {
-                        StackEntry e;
-                        if constexpr (JOB) e = shared_load_as(stk + q);
-                        else e = load_global(stk + q);
-                        cs_ra = e.n;
-                        cs_rem = e.remaining;
-                        cs_e = e.e;
-                        cs_m = e.m;
-                        cs_key = (Key)e.key;
-                    }
+                    // (lanes past the top read the top entry: a branch here
+                    // would make the compiler take lo, and with it the stack's
+                    // height and all that follows from it, for lane values)
+                    const uint32_t q = min(base + (((uint32_t)lane - base) & 63u), sp - 1u);
+                    StackEntry e;
+                    if constexpr (JOB) e = shared_load_as(stk + q);
+                    else e = load_global(stk + q);
+                    cs.ra = e.n;
+                    cs.rem = e.remaining;
+                    cs.e = e.e;
+                    cs.m = e.m;
+                    cs.key = (Key)e.key;
                     lo = base;
                 }
-                resume();
+                resume(last_ids());
                 n = length();
                 if (far_lo > n) far_lo = ~0u;
             }
@@ -1491,7 +1594,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         // end of the tour (or abort): back to the empty walk
         c_events += kb + li - 1u;
         const uint32_t n = length();
-        for (uint32_t i = 1u + (uint32_t)lane; i <= n; i += 64u) table[sid[i]] = (Key)0;
+        for (uint32_t i = 1u + (uint32_t)lane; i <= n; i += 64u) clear_id(sid[i]);
         wave_fence();
     }
     // (read again, so that the steps need not keep what only the end uses)
