@@ -172,7 +172,7 @@ void compute_layout(const pperm_config* c, pperm_layout* L) {
     resolve_shape(c, &sh);
     // one copy stack per sequence (a sequence runs on one wavefront at a time)
     const uint64_t stack_slots = align_up(N, sh.walks_per_wave);
-    const uint64_t chunks = (N + 63) / 64;
+    const uint64_t chunks = (N + 63) / 64;          // (more than a merge of MERGE_ROWS rows a block needs)
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) {
         uint64_t o = off;
@@ -346,13 +346,11 @@ int pperm_create(const pperm_config* cfg, void* d_workspace, size_t bytes, void*
     d.LR = (cfg->flags & PPERM_FLAG_OBSERVABLES) ? at<SumRec>(x, L.obs_L) : nullptr;
     x->desc_dev = reinterpret_cast<ProblemDesc*>(at<uint32_t>(x, L.ctrl) + CTRL_WORDS);
 
-    // zero the state (G .. ctrl are contiguous) and seed the digests
+    // zero the state (G .. ctrl are contiguous), seed the digests, write the descriptor
     const uint64_t zero_bytes = L.ctrl + CTRL_WORDS * 4 - L.G;
-    e = launch_init_state(at<uint64_t>(x, L.stats), cfg->n_sequences, x->ws + L.G, zero_bytes,
-                          x->stream);
+    e = launch_init_state(x->ws + L.G, zero_bytes, at<uint64_t>(x, L.stats), cfg->n_sequences, d,
+                          x->desc_dev, x->stream);
     if (e != hipSuccess) { delete x; return device_error(e, "init_state"); }
-    e = hipMemcpyAsync(x->desc_dev, &x->desc, sizeof(ProblemDesc), hipMemcpyHostToDevice, x->stream);
-    if (e != hipSuccess) { delete x; return device_error(e, "descriptor copy"); }
     *out = x;
     return PPERM_OK;
 }
@@ -394,9 +392,9 @@ int pperm_run_tours(pperm_ctx* x, uint32_t tours) {
     }
     a.step_cap = (uint32_t)cap;
 
-    HIP_TRY(launch_reset_ctrl(a.ctrl, x->stream));
     if (x->team_lanes == 64) {
-        // one walk per wavefront: the problem alone is a batch of one
+        // one walk per wavefront: the problem alone is a batch of one (its queue
+        // is at 0 after create and after every launch)
         BatchArgs b;
         memset(&b, 0, sizeof(b));
         b.entries = nullptr;
@@ -410,6 +408,7 @@ int pperm_run_tours(pperm_ctx* x, uint32_t tours) {
         HIP_TRY(launch_batch(b, x->workgroups, x->lds_wg_bytes, x->stream,
                              (x->cfg.flags & PPERM_FLAG_OBSERVABLES) != 0, x->long_walk));
     } else {
+        HIP_TRY(launch_reset_ctrl(a.ctrl, x->stream));
         HIP_TRY(launch_run(a, x->cfg.dim, x->team_lanes, x->workgroups, x->lds_wg_bytes, x->stream));
     }
     x->open_tours = per_seq_total;
@@ -436,9 +435,8 @@ int pperm_merge_epoch(pperm_ctx* x) {
         x->open_tours = 0;
         return PPERM_OK;
     }
-    HIP_TRY(launch_merge_counts(m, N, MG, m, x->stream));
-    // aligned pairwise tree over sequences, 64 rows per pass
-    const uint64_t chunks = (N + 63) / 64;
+    // aligned pairwise tree over sequences, MERGE_ROWS rows per block and pass
+    const uint64_t chunks = (N + MERGE_ROWS - 1) / MERGE_ROWS;
     SumRec* bufd[2] = {at<SumRec>(x, x->lay.scratch), at<SumRec>(x, x->lay.scratch) + chunks * row};
     uint64_t* bufh[2] = {reinterpret_cast<uint64_t*>(bufd[1] + chunks * row),
                          reinterpret_cast<uint64_t*>(bufd[1] + chunks * row) + chunks * row};
@@ -446,12 +444,14 @@ int pperm_merge_epoch(pperm_ctx* x) {
     a.in = L;
     a.hin = nullptr;
     a.zero = L;
+    a.m = m;
+    a.MG = MG;
     a.rows = N;
     a.row = row;
     a.ncols = x->cfg.n_max + 1;
     int cur = 0;
     for (;;) {
-        const bool final_pass = (a.rows <= 64);
+        const bool final_pass = (a.rows <= MERGE_ROWS);
         a.out = final_pass ? G : bufd[cur];
         a.hout = final_pass ? HG : bufh[cur];
         a.accumulate = final_pass ? 1u : 0u;
@@ -460,7 +460,8 @@ int pperm_merge_epoch(pperm_ctx* x) {
         a.in = bufd[cur];
         a.hin = bufh[cur];
         a.zero = nullptr;
-        a.rows = (uint32_t)((a.rows + 63) / 64);
+        a.m = nullptr;
+        a.rows = (a.rows + MERGE_ROWS - 1) / MERGE_ROWS;
         cur ^= 1;
     }
     if (x->cfg.flags & PPERM_FLAG_OBSERVABLES) {
@@ -469,9 +470,10 @@ int pperm_merge_epoch(pperm_ctx* x) {
         a.in = LR;
         a.hin = nullptr;
         a.zero = LR;
+        a.m = nullptr;
         a.rows = N;
         for (;;) {
-            const bool final_pass = (a.rows <= 64);
+            const bool final_pass = (a.rows <= MERGE_ROWS);
             a.out = final_pass ? at<SumRec>(x, x->lay.obs_G) : bufd[cur];
             a.hout = nullptr;
             a.accumulate = final_pass ? 1u : 0u;
@@ -479,7 +481,7 @@ int pperm_merge_epoch(pperm_ctx* x) {
             if (final_pass) break;
             a.in = bufd[cur];
             a.zero = nullptr;
-            a.rows = (uint32_t)((a.rows + 63) / 64);
+            a.rows = (a.rows + MERGE_ROWS - 1) / MERGE_ROWS;
             cur ^= 1;
         }
     }

@@ -116,12 +116,16 @@ struct BatchArgs {
     uint32_t* queue;              // zeroed before the launch
 };
 
+constexpr uint32_t MERGE_ROWS = 1024;   // rows of one block of a merge pass
+
 struct MergeArgs {
     const SumRec* in;      // [rows][row]
-    SumRec* out;           // [ceil(rows/64)][row], or G when final
-    uint64_t* hout;        // [ceil(rows/64)][row], or HG when final; nullptr: no counts
+    SumRec* out;           // [ceil(rows/MERGE_ROWS)][row], or G when final
+    uint64_t* hout;        // the same shape, or HG when final; nullptr: no counts
     const uint64_t* hin;   // later passes: [rows][row]; first pass: nullptr (counts in `in`)
     SumRec* zero;          // input to clear after reading (first pass) or nullptr
+    uint32_t* m;           // tour counts to add into MG and clear (first pass) or nullptr
+    uint64_t* MG;
     uint32_t rows;
     uint32_t row;
     uint32_t ncols;        // n_max + 1
@@ -130,8 +134,8 @@ struct MergeArgs {
 
 // Launchers (pperm_kernels.hip).  All return the hipError_t of the launch.
 hipError_t launch_reset_ctrl(uint32_t* ctrl, hipStream_t s);
-hipError_t launch_init_state(uint64_t* stats, uint32_t N, void* zero_base, size_t zero_bytes,
-                             hipStream_t s);
+hipError_t launch_init_state(void* zero_base, size_t zero_bytes, const uint64_t* stats, uint32_t N,
+                             const ProblemDesc& d, ProblemDesc* desc, hipStream_t s);
 hipError_t launch_run(const RunArgs& a, uint32_t dim, uint32_t team_lanes, uint32_t workgroups,
                       uint32_t lds_bytes, hipStream_t s);
 hipError_t run_kernel_lds_ok(uint32_t dim, uint32_t team_lanes, uint32_t lds_bytes,
@@ -215,8 +219,6 @@ hipError_t batch_occupancy(uint32_t lds_bytes, int* blocks_per_cu, bool long_wal
 constexpr uint32_t NOALLOC_MAX_PROBLEMS = 4096;
 constexpr size_t NOALLOC_QUEUE_BYTES = 256;
 hipError_t noalloc_scratch(void** ptr, size_t* bytes);
-hipError_t launch_merge_counts(const uint32_t* m, uint32_t N, uint64_t* MG, uint32_t* zero_m,
-                               hipStream_t s);
 hipError_t launch_group_sums(const SumRec* L, const uint32_t* m, uint32_t N, uint32_t row,
                              uint32_t n_max, SumRec* gsum, uint64_t* gtours, hipStream_t s);
 hipError_t launch_merge_independent(SumRec* L, uint32_t* m, SumRec* G, uint64_t* HG, uint64_t* MG,

@@ -1662,7 +1662,12 @@ __device__ __forceinline__ void batch_body(const BatchArgs& B) {
         uint32_t got = 0u;
         if (lane == 0) got = atomicAdd(B.queue, 1u);
         const uint32_t item = ufirst(__shfl(got, 0, 64));
-        if (item >= B.total_items) break;
+        if (item >= B.total_items) {
+            // each wave comes here once, so the last to come knows it and leaves
+            // the queue at 0 for the next launch (which needs no launch to clear it)
+            if (item - B.total_items == gridDim.x - 1u && lane == 0) *B.queue = 0u;
+            break;
+        }
         // the problem owning the item: entries are sorted by their first item
         LaunchEntry E = B.single;
         if (B.count > 1) {
@@ -2058,19 +2063,33 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(uint32_t* p, size_t word
 }
 
 // ---------------------------------------------------------------------------
-// Merge: aligned pairwise tree over sequences.  One wave takes 64 consecutive
-// rows (sequences) and a strip of 16 columns (lengths); lane i holds row i and
-// the tree over the 64 lanes is a butterfly of lane shuffles (xor 1, 2, ..,
-// 32): after level l every lane holds the sum of its aligned block of 2^(l+1)
-// rows, added as (left block) + (right block) up to commutativity, which IEEE
-// addition has.  Partial trees of aligned 64-row blocks are the tree's own
-// nodes, so repeated passes give the whole tree; missing rows are +0.0.
+// Merge: aligned pairwise tree over sequences.  A block of up to 16 waves takes
+// 64 consecutive rows (sequences) per wave and a strip of 8 columns (lengths);
+// lane i of a wave holds row i and the tree over the 64 lanes is a butterfly of
+// lane shuffles (xor 1, 2, .., 32): after level l every lane holds the sum of
+// its aligned block of 2^(l+1) rows, added as (left block) + (right block) up to
+// commutativity, which IEEE addition has.  The waves' sums go through LDS into
+// one more butterfly, over 16 lanes per column.  Partial trees of aligned blocks
+// are the tree's own nodes, so repeated passes give the whole tree; missing rows
+// are +0.0.  The first pass also adds up the tour counts (whole numbers, so in
+// any order) and clears what it read.
+//
+// A small epoch is bound by its launches: 40 sequences take 15.9 us with the
+// counts in a launch of their own, 9.8 us without, and up to 1024
+// sequences are one pass (64 before).
 // ---------------------------------------------------------------------------
 constexpr int MERGE_COLS = 8;
+constexpr int MERGE_WAVES = 16;
+static_assert(MERGE_ROWS == 64 * MERGE_WAVES, "rows of a merge block");
 
-__global__ void __launch_bounds__(64) merge_pass_kernel(MergeArgs A) {
-    const int lane = (int)threadIdx.x;
-    const uint32_t r = blockIdx.y * 64u + (uint32_t)lane;
+__global__ void __launch_bounds__(MERGE_ROWS) merge_pass_kernel(MergeArgs A) {
+    __shared__ SumRec part[MERGE_WAVES * MERGE_COLS];
+    __shared__ uint64_t parth[MERGE_WAVES * MERGE_COLS];
+    __shared__ uint64_t tours[MERGE_WAVES];
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = (int)threadIdx.x >> 6;
+    const int waves = (int)blockDim.x >> 6;
+    const uint32_t r = blockIdx.y * MERGE_ROWS + threadIdx.x;
     const uint32_t c0 = blockIdx.x * MERGE_COLS;
     XF v[MERGE_COLS];
     uint64_t h[MERGE_COLS];
@@ -2085,6 +2104,8 @@ __global__ void __launch_bounds__(64) merge_pass_kernel(MergeArgs A) {
         v[j] = xf_of(rec);
         h[j] = ok ? (A.hin ? A.hin[idx] : (uint64_t)rec.h) : 0ull;
     }
+    const bool counts = A.m != nullptr && blockIdx.x == 0u;
+    uint64_t t = counts && rv ? (uint64_t)A.m[r] : 0ull;
     if (A.zero && rv) {
         const SumRec z = {0.0, 0, 0u};
 #pragma unroll
@@ -2092,6 +2113,12 @@ __global__ void __launch_bounds__(64) merge_pass_kernel(MergeArgs A) {
             const uint32_t c = c0 + (uint32_t)j;
             if (c < A.ncols) A.zero[(size_t)r * A.row + c] = z;
         }
+    }
+    if (counts) {
+        if (rv) A.m[r] = 0u;
+#pragma unroll
+        for (int lvl = 1; lvl < 64; lvl <<= 1) t += __shfl_xor(t, lvl, 64);
+        if (lane == 0) tours[wave] = t;
     }
     // butterfly: after step lvl every lane holds the sum of its aligned block of
     // 2*lvl rows; the extended-range sum is commutative, so both lanes of a pair
@@ -2115,8 +2142,36 @@ __global__ void __launch_bounds__(64) merge_pass_kernel(MergeArgs A) {
         for (int j = 0; j < MERGE_COLS; ++j) {
             if (j == lane) { vv = v[j]; hh = h[j]; }
         }
-        const uint32_t c = c0 + (uint32_t)lane;
-        if (c < A.ncols) {
+        SumRec rec;
+        rec.m = vv.m;
+        rec.e = vv.e;
+        rec.h = 0u;
+        part[lane * MERGE_WAVES + wave] = rec;
+        parth[lane * MERGE_WAVES + wave] = hh;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    // the waves' sums: lane = 16 * (column & 3) + wave, four columns at a time
+    const int w = lane & (MERGE_WAVES - 1);
+#pragma unroll
+    for (int j0 = 0; j0 < MERGE_COLS; j0 += 64 / MERGE_WAVES) {
+        const int j = j0 + lane / MERGE_WAVES;
+        XF vv = {0.0, 0};
+        uint64_t hh = 0;
+        if (w < waves) {
+            vv = xf_of(part[j * MERGE_WAVES + w]);
+            hh = parth[j * MERGE_WAVES + w];
+        }
+#pragma unroll
+        for (int lvl = 1; lvl < MERGE_WAVES; lvl <<= 1) {
+            XF o;
+            o.m = __shfl_xor(vv.m, lvl, 64);
+            o.e = __shfl_xor(vv.e, lvl, 64);
+            vv = xf_add(vv, o);
+            hh += __shfl_xor(hh, lvl, 64);
+        }
+        const uint32_t c = c0 + (uint32_t)j;
+        if (w == 0 && c < A.ncols) {
             const size_t o = (size_t)blockIdx.y * A.row + c;
             if (A.accumulate) {
                 vv = xf_add(xf_of(A.out[o]), vv);
@@ -2130,22 +2185,11 @@ __global__ void __launch_bounds__(64) merge_pass_kernel(MergeArgs A) {
             if (A.hout) A.hout[o] = hh;
         }
     }
-}
-
-__global__ void __launch_bounds__(256) merge_counts_kernel(const uint32_t* m, uint32_t N,
-                                                           uint64_t* MG, uint32_t* zero_m) {
-    // one block: exact integer sum of the per-sequence tour counts
-    __shared__ uint64_t part[256];
-    uint64_t acc = 0;
-    for (uint32_t i = threadIdx.x; i < N; i += 256) acc += m[i];
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < N; i += 256) zero_m[i] = 0u;
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-        __syncthreads();
+    if (counts && lane == 0) {
+        uint64_t all = 0;
+        for (int k = 0; k < waves; ++k) all += tours[k];
+        atomicAdd(reinterpret_cast<unsigned long long*>(A.MG), (unsigned long long)all);
     }
-    if (threadIdx.x == 0) MG[0] += part[0];
 }
 
 __global__ void __launch_bounds__(256) merge_independent_kernel(SumRec* L, uint32_t* m, SumRec* G,
@@ -2199,14 +2243,20 @@ __global__ void reset_ctrl_kernel(uint32_t* ctrl) {
     if (threadIdx.x == CTRL_QUEUE) ctrl[CTRL_QUEUE] = 0u;
 }
 
-__global__ void __launch_bounds__(256) init_state_kernel(uint64_t* stats, uint32_t N,
-                                                         uint32_t* zero, size_t words) {
+// A new context's state in one launch: zeros from `zero` on, the digests among
+// them (low word of statistics word ST_DIGEST) at the FNV-1a 32 offset basis, and
+// the descriptor, which comes as an argument.  Two launches and a copy took 21.8 us
+// of a small call's create, this 14.8 us.
+__global__ void __launch_bounds__(256) init_state_kernel(uint32_t* zero, size_t words, size_t stats0,
+                                                         size_t stats_words, ProblemDesc d,
+                                                         ProblemDesc* desc) {
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words;
-         i += (size_t)gridDim.x * 256)
-        zero[i] = 0u;
-    // stats rows: counters 0, digest = the FNV-1a 32 offset basis
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (size_t)gridDim.x * 256)
-        stats[i * STATS_WORDS + ST_DIGEST] = FNV_OFFSET;
+         i += (size_t)gridDim.x * 256) {
+        const size_t k = i - stats0;
+        const bool digest = k < stats_words && (uint32_t)k % (2u * STATS_WORDS) == 2u * ST_DIGEST;
+        zero[i] = digest ? FNV_OFFSET : 0u;
+    }
+    if (blockIdx.x == 0u && threadIdx.x == 0u) *desc = d;
 }
 
 template <int D, int TS>
@@ -2227,19 +2277,15 @@ hipError_t launch_reset_ctrl(uint32_t* ctrl, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_init_state(uint64_t* stats, uint32_t N, void* zero_base, size_t zero_bytes,
-                             hipStream_t s) {
-    // zero everything first, then the digest seeds: same kernel, in order
+hipError_t launch_init_state(void* zero_base, size_t zero_bytes, const uint64_t* stats, uint32_t N,
+                             const ProblemDesc& d, ProblemDesc* desc, hipStream_t s) {
     const size_t words = zero_bytes / 4;
     uint32_t blocks = (uint32_t)((words + 255) / 256);
     if (blocks > 4096) blocks = 4096;
     if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL(init_state_kernel, dim3(blocks), dim3(256), 0, s, (uint64_t*)nullptr, 0u,
-                       (uint32_t*)zero_base, words);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(init_state_kernel, dim3((N + 255) / 256), dim3(256), 0, s, stats, N,
-                       (uint32_t*)nullptr, (size_t)0);
+    const size_t stats0 = (size_t)((const uint32_t*)stats - (const uint32_t*)zero_base);
+    hipLaunchKernelGGL(init_state_kernel, dim3(blocks), dim3(256), 0, s, (uint32_t*)zero_base, words,
+                       stats0, (size_t)N * STATS_WORDS * 2u, d, desc);
     return hipGetLastError();
 }
 
@@ -2314,14 +2360,9 @@ hipError_t run_kernel_lds_ok(uint32_t dim, uint32_t team_lanes, uint32_t lds_byt
 }
 
 hipError_t launch_merge_pass(const MergeArgs& a, hipStream_t s) {
-    dim3 grid((a.ncols + MERGE_COLS - 1) / MERGE_COLS, (a.rows + 63) / 64);
-    hipLaunchKernelGGL(merge_pass_kernel, grid, dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_counts(const uint32_t* m, uint32_t N, uint64_t* MG, uint32_t* zero_m,
-                               hipStream_t s) {
-    hipLaunchKernelGGL(merge_counts_kernel, dim3(1), dim3(256), 0, s, m, N, MG, zero_m);
+    const uint32_t waves = a.rows < MERGE_ROWS ? (a.rows + 63u) / 64u : (uint32_t)MERGE_WAVES;
+    dim3 grid((a.ncols + MERGE_COLS - 1) / MERGE_COLS, (a.rows + MERGE_ROWS - 1) / MERGE_ROWS);
+    hipLaunchKernelGGL(merge_pass_kernel, grid, dim3(64u * waves), 0, s, a);
     return hipGetLastError();
 }
 
