@@ -2250,8 +2250,10 @@ __global__ void reset_ctrl_kernel(uint32_t* ctrl) {
 __global__ void __launch_bounds__(256) init_state_kernel(uint32_t* zero, size_t words, size_t stats0,
                                                          size_t stats_words, ProblemDesc d,
                                                          ProblemDesc* desc) {
+    const size_t desc0 = (size_t)((const uint32_t*)desc - zero);
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words;
          i += (size_t)gridDim.x * 256) {
+        if (i - desc0 < sizeof(ProblemDesc) / 4) continue;      // (inside the range)
         const size_t k = i - stats0;
         const bool digest = k < stats_words && (uint32_t)k % (2u * STATS_WORDS) == 2u * ST_DIGEST;
         zero[i] = digest ? FNV_OFFSET : 0u;
