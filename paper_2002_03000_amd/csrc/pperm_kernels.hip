@@ -783,14 +783,6 @@ __device__ __forceinline__ uint32_t mask_count(uint64_t m, double x, int e, int 
     return r;
 }
 
-// The smaller of two numbers, without the compiler's NaN quieting around it (a
-// NaN operand gives the other one, two of them a NaN).
-__device__ __forceinline__ double min_f64(double a, double b) {
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 template <typename T>
 __device__ __forceinline__ uint32_t lds_address(T* p) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)p;
@@ -963,7 +955,7 @@ __device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
 // for a branch not taken, 20 for one taken, 16 where the scalar unit reads what
 // the vector unit wrote.  So the common event -- a walk with a free neighbour,
 // a decision that keeps one copy (or a survivor), a growth that ends neither
-// the walk, the random block nor the step budget -- is one straight block of 71
+// the walk, the random block nor the step budget -- is one straight block of 61
 // instructions, mostly vector code, with a single branch, its own loop's
 // (run_ahead); enrichment to two copies, pruning and trapping (a quarter of the
 // square lattice's events) are short blocks beside it; and everything else is
@@ -971,13 +963,18 @@ __device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
 // Measured (ms): with every case decided in line, 255 instructions and 17
 // branches a step / the straight block alone, 87 instructions / 78, with the
 // blocks beside it / 71, with the scalar unit's waits filled and every value of
-// the walk that is the same in all lanes known to be so:
-//   one square sequence of 20-step walks, 1000 tours       12.46 / 8.42 / 6.72 / 6.48
-//   4096 square sequences of 500 steps, 64 tours            94.6 / 70.2 / 47.6 / 46.5
-//   16384 cubic sequences of 1000 steps, 32 tours            198 /  149 /  101 / 98.9
-//   256 Rosenbluth walks of up to 6000 cubic steps, twice   6.41 / 3.40 / 2.15 / 1.97
-// A lone wave's step (us): square 0.625 -> 0.267, cubic 0.610 -> 0.259.
+// the walk that is the same in all lanes known to be so / 61, decided by the
+// hardware's reciprocal and a margin, the look-up first, the blocks beside it
+// without copies:
+//   one square sequence of 20-step walks, 1000 tours     12.46 / 8.42 / 6.72 / 6.48 / 6.23
+//   4096 square sequences of 500 steps, 64 tours          94.6 / 70.2 / 47.6 / 46.5 / 43.1
+//   16384 cubic sequences of 1000 steps, 32 tours          198 /  149 /  101 / 98.9 / 84.2
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 3.40 / 2.15 / 1.97 / 1.96
+// A lone wave's step (us): square 0.625 -> 0.240, cubic 0.610 -> 0.222.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
+// run_ahead's distance from a decision that the rounding of r could change: the
+// hardware's reciprocal is within 2^-24 and a uniform's high word within 2^-20.
+constexpr double DECISION_MARGIN = 0x1p-16;
 
 template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false>
 __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint32_t tours, uint32_t cap,
@@ -1123,8 +1120,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     const __amdgpu_buffer_rsrc_t row_out =
         __builtin_amdgcn_make_buffer_rsrc(Ls, 0, (int)(row * (uint32_t)sizeof(SumRec)), 0x00020000);
     const uint32_t lane_out = lane == 0 ? 0u : 0x80000000u;
-    // 2^-501 in a register (see run_ahead), and twice the lane
-    double small = 0x1p-501;
+    // -2^-501 in a register (see run_ahead), and twice the lane
+    double small = -0x1p-501;
     asm volatile("" : "+v"(small));
     const uint32_t lane2 = 2u * (uint32_t)lane;
 
@@ -1183,25 +1180,29 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         double wm, Lm;
         int we;
         SumRec G;
-        double uf = 0.0;                       // what run_ahead compares (see arm)
+        uint32_t uf = 0u;                      // what run_ahead compares (see arm)
         SumRec nxt = {0.0, 0, 0u}, nxr = {0.0, 0, 0u};   // records of the next length
         auto steps = [&]() INLINE { return (uint32_t)c_events + kb + li - 1u - c_prunes; };
-        // Makes the next events ready for run_ahead: lane i of uf holds the
-        // uniform of its event, but at least 1/16 (survival at a ratio below
-        // that, which could scale wm without limit, is decided outside, as is a
-        // uniform of 0), and no number (which fails every test) from the event
-        // on that could end the walk or the step budget, or at once while some site is
-        // outside its places.  (After a resume the walk's end is further off
-        // than this says, which only stops run_ahead for nothing.)
+        // Makes the next events ready for run_ahead: lane i of uf holds the high
+        // word of 1 - u - MARGIN, u the uniform of its event, but at least 1/16
+        // (survival at a ratio below that, which could scale wm without limit,
+        // is decided outside, as is a uniform of 0), and no number (which fails
+        // every test) from the event on that could end the walk or the step
+        // budget, or at once while some site is outside its places.  (After a
+        // resume the walk's end is further off than this says, which only stops
+        // run_ahead for nothing.)
         auto arm = [&](uint32_t n) INLINE {
             const uint32_t left = min(n_max - n, capv - steps());
             const uint32_t last = far_lo != ~0u ? li : li + left - 1u;
-            const double uu = u < 0.0625 ? 0.0625 : u;
-            uf = ((uint32_t)lane >= last || lane == 0) ? __builtin_nan("") : uu;
+            const double uc = (1.0 - DECISION_MARGIN) - (u < 0.0625 ? 0.0625 : u);
+            uf = ((uint32_t)lane >= last || lane == 0) ? 0x7FF80000u : (uint32_t)__double2hiint(uc);
         };
-        // (LONG) the next length's records, from global memory
+        // the next length's records
         auto load_next = [&]() INLINE {
-            if constexpr (LONG) {
+            if constexpr (!LONG) {
+                nxt = record_of(lds_load<u32x4>(ra + 16u));
+                if constexpr (OBS) nxr = record_of(lds_load<u32x4>(ra + 16u + row_lds));
+            } else {
                 nxt = load_global(reinterpret_cast<const SumRec*>(reinterpret_cast<const unsigned char*>(Ls) + ra) + 1);
                 if constexpr (OBS)
                     nxr = load_global(
@@ -1229,12 +1230,15 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         // what scan leaves: the neighbours' keys, slots and contents, the hits,
         // a_+, the choice, and the decision
         Key nk, v;
-        uint32_t place, a, x, il, a8, id, hn;
+        uint32_t place, a, il, a8, id, hn;
         uint64_t hits, pick, choice, below1 = 0ull;
-        double t, ut, uu, r = 0.0, w1, af;
+        double t, ut, uu, r1 = 0.0, w1, af;
         SumRec nx2 = {0.0, 0, 0u}, nr2 = {0.0, 0, 0u};
-        auto scan = [&](auto decide) INLINE {
-            // occupancy reads, the next length's record and pooled sum
+        auto fold = [&]() INLINE { digest = (digest ^ ((il >> LW) | a8)) * FNV_PRIME; };
+        // (grown: right after commit, whose digest is left for where the look-up
+        // takes its time)
+        auto scan = [&](auto decide, auto grown) INLINE {
+            // occupancy reads, the next length's pooled sum
             nk = S_::next(ekey, pdelta);
             place = place_of(nk);
             v = lds_load<Key>(place);
@@ -1246,45 +1250,48 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 if constexpr (OBS)
                     nr2 = load_global(
                         reinterpret_cast<const SumRec*>(reinterpret_cast<const unsigned char*>(LRs) + ra) + 2);
-            } else {
-                nxt = record_of(lds_load<u32x4>(ra + 16u));
-                if constexpr (OBS) nxr = record_of(lds_load<u32x4>(ra + 16u + row_lds));
             }
-            uu = lane_value(uf, li);
-            double thr = 1.0;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (decltype(grown)::value) fold();
+            uu = __hiloint2double((int)lane_value(uf, li), 0);
+            const uint32_t bl = lane_value(b0, li);
             w1 = wm;
             if constexpr (decltype(decide)::value) {
                 // eqn (6): r = W / [W_n], [W_n] = sum / seen (own epoch
                 // data weighted N in Algorithm 2), as (W * seen) / sum.
                 // One copy goes on iff u < r < 1 (a survivor, which takes
-                // sum / seen) or 1 <= r < 2 and u < 2 - r.
+                // sum / seen) or 1 <= r < 2 and u < 2 - r: iff |r - 1| < 1 - u.
+                // The hardware's reciprocal gives r - 1 well within the margin
+                // that uf holds back; what falls between is decided outside, as
+                // is r < 1 here, from the quotient as IEEE rounds it (which is
+                // below 1 iff W * seen < sum).
                 const double sum = ldexp(G.m, G.e - we) + Lm * pool;
-                r = div_by(wm * seen, sum, recip_normal(sum));
-                thr = min_f64(r, 2.0 - r);
+                const double ww = wm * seen;
+                r1 = __builtin_fma(ww, __builtin_amdgcn_rcp(sum), -1.0);
                 const double ws = div_by(sum, seen, seen_r);
-                below1 = __ballot(r < 1.0);
-                w1 = r < 1.0 ? ws : wm;
+                below1 = __ballot(ww < sum);
+                w1 = ww < sum ? ws : wm;
                 G = pooled(ra, 1u);
             }
             __builtin_amdgcn_sched_barrier(0);
             hits = __ballot(v == nk);
             // (and the next length's sum at this scale)
             a = (uint32_t)(2 * D) - mask_count(hits, nxt.m, nxt.e, we, t);
-            // The j-th free neighbour, j = floor(B0 a / 2^32): the number
-            // of free directions below a lane's own is pdir less the hits
-            // in lanes below it, so x is 0 in the chosen direction's
-            // lanes (and in lanes of occupied neighbours of it: those up
-            // to the hit, which are not empty, before it, those past the
-            // hit after it).  Its first empty place is the lowest lane
-            // with x = 0 that read an empty slot.
-            const uint32_t j = __umulhi(lane_value(b0, li), a);
-            x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j - (uint32_t)pdir));
-            pick = __ballot((x | S_::mark(v)) == 0u);
-            // (the term that adds the next sum to u is below u's last place
-            // unless the sum is 2^440 times the weight or more, which stops here)
+            // The j-th free neighbour, j = floor(B0 a / 2^32): j and the
+            // hits in lanes below a lane's own make its direction in the
+            // chosen direction's lanes (and in lanes of occupied neighbours
+            // of it: those up to the hit, which are not empty, before it,
+            // those past the hit after it).  Its first empty place is the
+            // lowest such lane that read an empty slot.
+            const uint32_t j = __umulhi(bl, a);
+            const uint32_t x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j));
+            pick = __ballot(((x ^ (uint32_t)pdir) | S_::mark(v)) == 0u);
+            // (the term that takes the next sum from 1 - u is below its last
+            // place unless the sum is 2^440 times the weight or more, which
+            // stops here)
             ut = __builtin_fma(t, small, uu);
-            const uint64_t ok = __ballot(ut < thr);
+            const uint64_t ok = __ballot(__builtin_fabs(r1) < ut);
             __builtin_amdgcn_sched_barrier(0);
             // what growth needs whoever is chosen, while the scalar unit waits
             af = (double)a;
@@ -1308,6 +1315,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             sa += 2u;
             li += 1u;
             const u32x4 rec = words_of(Lm, we, hn);
+            if constexpr (!LONG) nxt = record_of(lds_load<u32x4>(ra + 16u));
             if constexpr (LONG) {
                 write_site(il, place, nk, sa, id);
                 __builtin_amdgcn_raw_buffer_store_b128(rec, row_out, ra | lane_out, 0, 0);
@@ -1331,10 +1339,11 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                         *reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds + (ra - rec_base)) = rr;
                 }
             }
-            digest = (digest ^ ((il >> LW) | a8)) * FNV_PRIME;
             if constexpr (LONG) {
                 nxt = nx2;
                 if constexpr (OBS) nxr = nr2;
+            } else {
+                if constexpr (OBS) nxr = record_of(lds_load<u32x4>(ra + 16u + row_lds));
             }
         };
         // a copy stack entry: `copies` still to resume here with weight w
@@ -1363,66 +1372,80 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             const uint32_t end = sa;
             sa = (ra >> 3) + (sid_base - rec_base / 8u);
             clear_sites<Key>(lane2, end - sa, at * (uint32_t)sizeof(Key));
-            for (uint32_t d = 128u; __ballot(end - sa > d) != 0ull; d += 128u) {
-                at = lds_load<uint16_t>(end - d - lane2);
-                clear_sites<Key>(lane2 + d, end - sa, at * (uint32_t)sizeof(Key));
+            if (__builtin_expect(__ballot(end - sa > 128u) != 0ull, 0)) {
+                uint32_t d = 128u;
+                do {
+                    at = lds_load<uint16_t>(end - d - lane2);
+                    clear_sites<Key>(lane2 + d, end - sa, at * (uint32_t)sizeof(Key));
+                    d += 128u;
+                } while (__ballot(end - sa > d) != 0ull);
             }
-            sp -= rem == 1u ? 1u : 0u;         // its last copy: the entry is done
+            sp += min(rem - 1u, 1u) - 1u;      // its last copy: the entry is done
             no_decision();
             load_next();
         };
-        // Runs common events, the enrichments that make two copies and the
-        // prunings, until an event needs more: false, the event at li is still
-        // to be handled; true, a copy ended and no pending one is in registers.
-        // (No variable is declared inside its loop, and all its ways out are
-        // one: blocks that only tell them apart would each copy everything a
-        // step changes.)
-        uint32_t pruned, ended, at;
-        auto run_ahead = [&](auto decide) INLINE -> bool {
-            ended = 0u;
-            for (;;) {
-                scan(decide);
+        // Runs common events, and with decisions also the enrichments that make
+        // two copies and the prunings and traps that a pending copy in registers
+        // follows, until an event needs more.  (The compiler lays loops out with
+        // their exit at the end and if-else as two ifs, and copies what a branch
+        // changes where that is not how they are written; hence the form.  No
+        // variable is declared inside, for the same reason.)
+        uint64_t trap, sure = 0ull;
+        uint32_t at = 0u, il2 = 0u, ends, two, back;
+        auto run_ahead = [&](auto decide) INLINE {
+            two = back = 0u;
+            do {
+                if (two != 0u) {
+                    // 1 <= r < 2 and u >= 2 - r
+                    il = il2;
+                    push(0.5 * wm, 1u);
+                    commit(0.5 * wm);
+                    fold();
+                }
+                if (back != 0u) {
+                    // u >= r, pruned with probability 1 - r, or a trap (masks of
+                    // all lanes: -1 or 0)
+                    c_traps -= (uint32_t)trap;
+                    c_prunes -= ~(uint32_t)trap;
+                    li -= ~(uint32_t)trap;
+                    resume(at);
+                }
+                scan(decide, no{});
                 while (chosen()) {
                     commit(w1);
-                    scan(decide);
+                    scan(decide, yes{});
                 }
+                // no free neighbour: a trap, and no event
+                trap = __ballot(a == 0u);
                 if constexpr (decltype(decide)::value) {
-                    // (a ratio out of range, a uniform that is not the event's or
-                    // a sum out of range: no number passes)
                     at = last_ids();           // (for resume, while the tests wait)
-                    if ((__ballot(r > 0.0625) & __ballot(r < 1.9375) & __ballot(ut == uu)) == 0ull) break;
-                    if (choice != 0ull) break; // the decision was common: all places taken
-                    if (below1 == 0ull) {
-                        // 1 <= r < 2 and u >= 2 - r: two copies
-                        il = first_bit(pick);
-                        if (!chosen()) break;  // (no free neighbour, or no free place)
-                        if (sp - lo == 64u) break;
-                        push(0.5 * wm, 1u);
-                        commit(0.5 * wm);
-                        continue;
-                    }
-                    // u >= r, pruned with probability 1 - r, unless no neighbour
-                    // is free: a trap, and no event
-                    pruned = pick != 0ull ? 1u : 0u;
-                } else {
-                    if (pick != 0ull || li == 64u) break;
-                    at = last_ids();
-                    pruned = 0u;
+                    // (a ratio out of range or too near the uniform, a uniform that
+                    // is not the event's or a sum out of range: no number passes;
+                    // nor does a common decision, all places taken)
+                    sure = (__ballot(__builtin_fabs(r1) < 0.9375) &
+                            __ballot(__builtin_fabs(r1) > uu + 4.0 * DECISION_MARGIN) & __ballot(ut == uu)) | trap;
+                    il2 = first_bit(pick);
+                    ends = (uint32_t)(below1 | trap);
+                    // two copies need a place for the grown one and one in the
+                    // stack's registers, everything else a copy there to go back to
+                    two = min(64u - (sp - lo), ~il2 & (uint32_t)(W - 1)) & (uint32_t)sure & ~ends;
+                    back = (sp - lo) & (uint32_t)sure & ends;
+                    asm volatile("" : "+s"(two), "+s"(back));
                 }
-                c_prunes += pruned;
-                c_traps += 1u - pruned;
-                li += pruned;
-                if (sp == lo) {
-                    ended = 1u;
-                    break;
-                }
-                resume(at);
-            }
-            return ufirst(ended) != 0u;
+            } while ((two | back) != 0u);
         };
 
         for (;;) {
-            bool bt = control_mode ? run_ahead(yes{}) : run_ahead(no{});
+            if (control_mode) run_ahead(yes{});
+            else run_ahead(no{});
+            // the walk has ended here: trapped, or certainly pruned
+            bool bt = trap != 0ull;
+            c_traps += bt ? 1u : 0u;
+            if (!bt && sure != 0ull && below1 != 0ull) {
+                c_prunes += 1u;
+                li += 1u;
+                bt = true;
+            }
             if (!bt && li == 64u) {
                 // ---- the next random blocks ----
                 kb += 63u;
@@ -1454,6 +1477,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 const uint32_t au = (uint32_t)(2 * D) - (uint32_t)__popcll(hits | outside);
                 XF w = xf_norm_nz(wm, we);
                 if (au == 0u) {
+                    // (a site outside its places closes the trap)
                     c_traps += 1u;
                     bt = true;
                 } else if (control_mode && __ballot(Lm != 0.0) != 0ull) {
@@ -1500,16 +1524,21 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     }
                 }
                 if (!bt) {
-                    if (far_lo != ~0u) {
-                        const uint64_t occ = hits | outside;
-                        const uint32_t j = __umulhi(lane_value(b0, li), au);
-                        x = __builtin_amdgcn_mbcnt_hi((uint32_t)(occ >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)occ, j - (uint32_t)pdir));
-                    }
-                    il = (uint32_t)__builtin_ctzll(__ballot((x | S_::mark(v)) == 0u) & ~outside);
-                    ekey = lane_value(nk, il);
-                    uint32_t ins = lane_value(place, il);
-                    if (!chosen()) {
+                    // the chosen direction, by its last lane (every hit of the
+                    // directions before it is in a lane below)
+                    const uint64_t occ = hits | outside;
+                    const uint32_t j = __umulhi(lane_value(b0, li), au);
+                    const uint32_t x = __builtin_amdgcn_mbcnt_hi((uint32_t)(occ >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)occ, j));
+                    const uint64_t last =
+                        __ballot(x == (uint32_t)(lane / W) && poff == W - 1) & ~outside;
+                    const uint32_t first = (uint32_t)__builtin_ctzll(last) & ~(uint32_t)(W - 1);
+                    ekey = lane_value(nk, first);
+                    const uint64_t places = __ballot(S_::mark(v) == 0u) & ((FIELD >> 1) << first);
+                    uint32_t ins = 0u;
+                    if (places != 0ull) {
+                        ins = lane_value(place, (uint32_t)__builtin_ctzll(places));
+                    } else {
                         // all places taken: the first empty slot of the table
                         // (slots outnumber the sites of the longest walk)
                         for (uint32_t b = 0;; b += 64u) {
@@ -1523,7 +1552,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                         }
                         far_lo = min(far_lo, n + 1u);
                     }
-                    digest = (digest ^ ((il >> LW) | (au << 3))) * FNV_PRIME;
+                    digest = (digest ^ ((first >> LW) | (au << 3))) * FNV_PRIME;
                     w = xf_mul_nz(w, (double)au);
                     n += 1u;
                     ra += 16u;
@@ -1560,8 +1589,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     // number, and the decision comes here)
                     weigh(w);
                     Lm = ldexp(Lnew.m, Lnew.e - we);
-                    load_next();
                     bt = n == n_max;
+                    if (!bt) load_next();
                 }
             }
             if (bt) {
