@@ -965,12 +965,12 @@ __device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
 // blocks beside it / 71, with the scalar unit's waits filled and every value of
 // the walk that is the same in all lanes known to be so / 61, decided by the
 // hardware's reciprocal and a margin, the look-up first, the blocks beside it
-// without copies:
-//   one square sequence of 20-step walks, 1000 tours     12.46 / 8.42 / 6.72 / 6.48 / 6.23
-//   4096 square sequences of 500 steps, 64 tours          94.6 / 70.2 / 47.6 / 46.5 / 43.1
-//   16384 cubic sequences of 1000 steps, 32 tours          198 /  149 /  101 / 98.9 / 84.2
-//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 3.40 / 2.15 / 1.97 / 1.96
-// A lone wave's step (us): square 0.625 -> 0.240, cubic 0.610 -> 0.222.
+// without copies / with full walks stopped by a guard record:
+//   one square sequence of 20-step walks, 1000 tours     12.46 / 8.42 / 6.72 / 6.48 / 6.23 / 5.26
+//   4096 square sequences of 500 steps, 64 tours          94.6 / 70.2 / 47.6 / 46.5 / 42.3 / 41.6
+//   16384 cubic sequences of 1000 steps, 32 tours          198 /  149 /  101 / 98.9 / 86.8 / 86.3
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 3.40 / 2.15 / 1.97 / 1.96 / 1.94
+// A lone wave's step (us): square 0.625 -> 0.235, cubic 0.610 -> 0.213.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 // run_ahead's distance from a decision that the rounding of r could change: the
 // hardware's reciprocal is within 2^-24 and a uniform's high word within 2^-20.
@@ -1089,6 +1089,13 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) LRs[i] = load_global(P.LR + rb0 + i);
         }
     }
+    // In LDS, a row padded to 16 records has a record past the last length's. No
+    // number there makes every test of run_ahead fail at n_max: the walk stops
+    // there without having been watched.
+    const bool guarded = !LONG && row > n_max + 1u;
+    if constexpr (!LONG) {
+        if (guarded && lane == 0) Ls[n_max + 1u] = SumRec{__builtin_nan(""), 0, 0u};
+    }
     wave_fence();
     SumRec rec0 = rec_ld(Ls);
     // counters of this call, added to the sequence's totals at its end
@@ -1187,13 +1194,13 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         // word of 1 - u - MARGIN, u the uniform of its event, but at least 1/16
         // (survival at a ratio below that, which could scale wm without limit,
         // is decided outside, as is a uniform of 0), and no number (which fails
-        // every test) from the event on that could end the walk or the step
-        // budget, or at once while some site is outside its places.  (After a
-        // resume the walk's end is further off than this says, which only stops
-        // run_ahead for nothing.)
+        // every test) from the event on that could end the step budget or, with no
+        // guard, the walk, or at once while some site is outside its places.
+        // (After a resume the walk's end is further off than this says, which only
+        // stops run_ahead for nothing.)
         auto arm = [&](uint32_t n) INLINE {
-            const uint32_t left = min(n_max - n, capv - steps());
-            const uint32_t last = far_lo != ~0u ? li : li + left - 1u;
+            const uint32_t left = min(guarded ? ~0u : n_max - n, capv - steps());
+            const uint32_t last = far_lo != ~0u ? li : li + min(left, 64u) - 1u;
             const double uc = (1.0 - DECISION_MARGIN) - (u < 0.0625 ? 0.0625 : u);
             uf = ((uint32_t)lane >= last || lane == 0) ? 0x7FF80000u : (uint32_t)__double2hiint(uc);
         };
@@ -1415,15 +1422,17 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     commit(w1);
                     scan(decide, yes{});
                 }
-                // no free neighbour: a trap, and no event
-                trap = __ballot(a == 0u);
+                // no free neighbour: a trap, and no event (at n_max no number is
+                // equal to itself)
+                const uint64_t plain = __ballot(ut == uu);
+                trap = __ballot(a == 0u) & plain;
                 if constexpr (decltype(decide)::value) {
                     at = last_ids();           // (for resume, while the tests wait)
                     // (a ratio out of range or too near the uniform, a uniform that
                     // is not the event's or a sum out of range: no number passes;
                     // nor does a common decision, all places taken)
                     sure = (__ballot(__builtin_fabs(r1) < 0.9375) &
-                            __ballot(__builtin_fabs(r1) > uu + 4.0 * DECISION_MARGIN) & __ballot(ut == uu)) | trap;
+                            __ballot(__builtin_fabs(r1) > uu + 4.0 * DECISION_MARGIN) & plain) | trap;
                     il2 = first_bit(pick);
                     ends = (uint32_t)(below1 | trap);
                     // two copies need a place for the grown one and one in the
@@ -1446,6 +1455,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 li += 1u;
                 bt = true;
             }
+            uint32_t n = length();
+            bt = bt || n == n_max;
             if (!bt && li == 64u) {
                 // ---- the next random blocks ----
                 kb += 63u;
@@ -1457,10 +1468,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 // (scan has moved on to the next length's sum)
                 if (__ballot(Lm != 0.0) != 0ull) G = pooled(ra, 0u);
                 else no_decision();
-                arm(length());
+                arm(n);
                 continue;
             }
-            uint32_t n = length();
             if (!bt) {
                 // ---- one event with every case ----
                 uint64_t outside = 0ull;       // directions found outside their places (last lanes)

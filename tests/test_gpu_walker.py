@@ -64,3 +64,21 @@ def test_step_cap_stops_at_the_step(cap):
     for f in ("steps", "events", "digest", "capped", "tours"):
         assert np.array_equal(st[f], o.stats[f]), f
     assert st["capped"].any()
+
+
+@pytest.mark.parametrize("n_max", [14, 15, 16, 30, 31])
+@pytest.mark.parametrize("mode", ["shared", "rosenbluth"])
+def test_walks_stop_at_n_max_with_and_without_a_guard_record(n_max, mode):
+    # (rows are padded to 16 records: 15 and 31 leave no room for the guard)
+    codes = {"shared": oracle.MODE_SHARED, "rosenbluth": oracle.MODE_ROSENBLUTH}
+    from paper_2002_03000_amd import ParallelFlatPERM
+    for obs in (False, True):
+        g = ParallelFlatPERM(2, n_max, 60, 94, mode=mode, observables=obs)
+        o = oracle.Oracle(2, n_max, 60, 94, mode=codes[mode], observables=obs)
+        for T in (1, 9):
+            g.run_tours(T)
+            o.run_tours(T)
+            assert_epoch_equal(g, o, label=f"n_max={n_max}")
+            g.merge_epoch()
+            o.merge_epoch()
+            assert_pooled_equal(g, o, f"n_max={n_max}")
