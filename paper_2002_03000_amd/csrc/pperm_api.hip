@@ -374,6 +374,38 @@ int pperm_create(const pperm_config* cfg, void* d_workspace, size_t bytes, void*
     return PPERM_OK;
 }
 
+// Whether the tours of one call go out as parts of sequences (part_body), and how:
+// where more sequences than fit at once have enough steps each.  A part is a
+// quarter of the tours, or more where that is under 2048 steps (about 0.5 ms; a
+// hand-over takes some 20 us), its list lies in the merge's scratch, which a run does
+// not use, and the rows of long walks in the stacks of the sequences past the
+// first `workgroups` (a stack belongs to a wave here, not to a sequence).
+static bool plan_parts(pperm_ctx* x, uint32_t tours, PartArgs* a) {
+    const uint64_t N = x->cfg.n_sequences, n1 = x->cfg.n_max + 1ull, wgs = x->workgroups;
+    if (N <= wgs || N >= PART_MAX_N - 1u || (x->cfg.flags & PPERM_FLAG_OBSERVABLES)) return false;
+    const uint64_t room = x->lay.total - x->lay.scratch;
+    uint64_t part = std::max<uint64_t>((tours + PART_MAX - 1ull) / PART_MAX, (2048ull + n1 - 1ull) / n1), parts;
+    for (;; part *= 2ull) {
+        parts = (tours + part - 1ull) / part;
+        if (parts < 2ull) return false;
+        if (8ull * (1ull + N * (parts - 1ull)) <= room) break;
+    }
+    if (N * parts + wgs > 0xFFFFFFFFull) return false;
+    a->wave_rows = nullptr;
+    if (x->long_walk) {
+        const uint64_t per = x->cfg.n_max * (uint64_t)sizeof(StackEntry);
+        const uint64_t first = align_up(wgs * per, 256);
+        // (and one record more, which a walk near its end reads and does not use)
+        if (first + (wgs * x->lay.row + 1ull) * sizeof(SumRec) > x->lay.stack_slots * per) return false;
+        a->wave_rows = reinterpret_cast<SumRec*>(x->ws + x->lay.stack + first);
+    }
+    a->list = at<uint64_t>(x, x->lay.scratch);
+    a->tours = tours;
+    a->part_tours = (uint32_t)part;
+    a->parts = (uint32_t)parts;
+    return true;
+}
+
 int pperm_run_tours(pperm_ctx* x, uint32_t tours) {
     if (!x || tours == 0) return PPERM_EINVAL;
     const uint64_t N = x->cfg.n_sequences;
@@ -411,7 +443,14 @@ int pperm_run_tours(pperm_ctx* x, uint32_t tours) {
     }
     a.step_cap = (uint32_t)cap;
 
-    if (x->team_lanes == 64) {
+    PartArgs parts;
+    if (x->team_lanes == 64 && plan_parts(x, tours, &parts)) {
+        parts.desc = x->desc_dev;
+        parts.queue = a.ctrl + CTRL_QUEUE;
+        parts.step_cap = a.step_cap;
+        HIP_TRY(launch_fill_zero(parts.list, 8ull * (1ull + (uint64_t)a.N * (parts.parts - 1u)), x->stream));
+        HIP_TRY(launch_parts(parts, x->workgroups, x->lds_wg_bytes, x->stream, x->long_walk));
+    } else if (x->team_lanes == 64) {
         // one walk per wavefront: the problem alone is a batch of one (its queue
         // is at 0 after create and after every launch)
         BatchArgs b;

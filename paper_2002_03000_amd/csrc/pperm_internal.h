@@ -116,6 +116,19 @@ struct BatchArgs {
     uint32_t* queue;              // zeroed before the launch
 };
 
+// A launch whose work items are parts of a sequence's tours (part_body).  list: a
+// count of entries, then one entry per sequence and part after the first, all
+// zero before the launch: the rest of the step cap (32 bits), the part, and the
+// sequence plus one (in PART_MAX_N).
+constexpr uint32_t PART_MAX_N = 1u << 26, PART_MAX = 4;
+struct PartArgs {
+    const ProblemDesc* desc;
+    uint32_t* queue;
+    uint64_t* list;
+    SumRec* wave_rows;     // long walks: one row per workgroup
+    uint32_t tours, part_tours, parts, step_cap;
+};
+
 constexpr uint32_t MERGE_ROWS = 1024;   // rows of one block of a merge pass
 
 struct MergeArgs {
@@ -198,6 +211,7 @@ struct JobArgs {
     uint64_t slice_ticks;     // 100 MHz ticks after which no epoch starts, 0: none
 };
 
+hipError_t launch_parts(const PartArgs& a, uint32_t workgroups, uint32_t lds_bytes, hipStream_t s, bool long_walk);
 hipError_t launch_job(const JobArgs& a, uint32_t workgroups, uint32_t lds_bytes, hipStream_t s);
 // After a whole-schedule launch: flag the context of every problem whose
 // epochs did not all run (ERR_INCOMPLETE) and count them.

@@ -945,6 +945,8 @@ __device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
 // LONG in the global row) and another wave may have run its last epoch.
 // OBS: also record W * R^2 (squared end-to-end distance) at every arrival
 // beside the weight, the numerator of the ratio estimator of eqn (5).
+// PART: some of a sequence's tours, with its state handed on past the L2 (wave_row:
+// with LONG, a row of this wave's own for the sums; left: the rest of the step cap).
 // LONG: walks too long for the per-length sums to share LDS with the
 // occupancy table; the sums stay in the sequence's global row (read and
 // written in place) and LDS holds the table and the slot ids.
@@ -976,10 +978,12 @@ constexpr uint32_t WALK_ABORTED = 0x80000000u;
 // hardware's reciprocal is within 2^-24 and a uniform's high word within 2^-20.
 constexpr double DECISION_MARGIN = 0x1p-16;
 
-template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false>
+template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false, bool PART = false>
 __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint32_t tours, uint32_t cap,
-                                                  uint32_t s, unsigned char* lds, const SumRec* Gsrc) {
-    static_assert(!(OBS && JOB), "chained launches keep no observables");
+                                                  uint32_t s, unsigned char* lds, const SumRec* Gsrc,
+                                                  SumRec* wave_row = nullptr, uint32_t* left = nullptr) {
+    static_assert(!(OBS && (JOB || PART)) && !(JOB && PART), "not built");
+    constexpr bool HANDED = JOB || PART;       // another wave may have run the sequence before
     // (loads through a generic pointer pass for lane values)
     tours = ufirst(tours);
     cap = ufirst(cap);
@@ -997,7 +1001,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     Key* table = reinterpret_cast<Key*>(lds);
     uint16_t* sid = reinterpret_cast<uint16_t*>(lds + sizeof(Key) * P.slots);
     const uint32_t row_lds = LONG ? 0u : P.row * (uint32_t)sizeof(SumRec);
-    SumRec* Ls = LONG ? P.L + (size_t)s * P.row : reinterpret_cast<SumRec*>(lds + P.lds_team_bytes);
+    SumRec* Ls = !LONG ? reinterpret_cast<SumRec*>(lds + P.lds_team_bytes)
+                       : PART ? wave_row : P.L + (size_t)s * P.row;
     // (observables) the sequence's per-length sums of W * R^2, after its sums
     SumRec* LRs = LONG ? P.LR + (size_t)s * P.row
                        : reinterpret_cast<SumRec*>(lds + P.lds_team_bytes + row_lds);
@@ -1072,17 +1077,20 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     wave_fence();
 
     // the copy stack of sequence s
-    StackEntry* stk = P.stack + (size_t)s * n_max;
+    StackEntry* stk = P.stack + (size_t)(PART ? blockIdx.x : s) * n_max;
     uint64_t MGs = 0ull;
     if (shared_mode) MGs = JOB ? ufirst64(shared_load(P.MG)) : P.MG[0];
 
     const size_t rb0 = (size_t)s * row;
     const SumRec* Grow = shared_mode ? Gsrc : Gsrc + rb0;
     if (!shared_mode) MGs = ufirst64(P.MG[s]);
-    uint32_t tlo = ufirst((uint32_t)(JOB ? shared_load(P.t + s) : P.t[s]));   // tour index: its low word keys the random numbers
-    uint32_t m = JOB ? 0u : ufirst(P.m[s]);
+    uint32_t tlo = ufirst((uint32_t)(HANDED ? shared_load(P.t + s) : P.t[s]));   // tour index: its low word keys the random numbers
+    uint32_t m = JOB ? 0u : ufirst(PART ? shared_load(P.m + s) : P.m[s]);
     if constexpr (JOB) {
         for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) rec_st(Ls + i, SumRec{0.0, 0, 0u});
+    } else if constexpr (PART) {
+#pragma unroll 4
+        for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) rec_st(Ls + i, shared_load_as(P.L + rb0 + i));
     } else if constexpr (!LONG) {
         for (uint32_t i = (uint32_t)lane; i <= n_max; i += 64u) Ls[i] = load_global(P.L + rb0 + i);
         if constexpr (OBS) {
@@ -1105,7 +1113,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     uint64_t c_copies = 0, c_events = 0;
     const uint32_t capv = cap ? cap : 0xFFFFFFFFu;   // step cap of this call (0: none)
     const uint64_t* old_digest = P.stats + (size_t)s * STATS_WORDS + ST_DIGEST;
-    uint32_t digest = (uint32_t)(JOB ? shared_load(old_digest) : *old_digest) + vz;
+    uint32_t digest = (uint32_t)(HANDED ? shared_load(old_digest) : *old_digest) + vz;
     bool abort = false;
     // the registers of the copy stack (see the tour loop)
     CopyLanes<Key> cs = {0u, 0u, 0, 0.0, (Key)0};
@@ -1646,6 +1654,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         r.m = v.m;
         r.e = v.e;
         if constexpr (JOB) rec_st(p, r);
+        else if constexpr (PART) shared_store_as(out, r);
         else store_global(out, r);
     };
     if (lane == 0) rec_st(Ls, rec0);
@@ -1658,8 +1667,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     wave_fence();
     if (lane == 0) {
         if (abort) atomicOr(&Q.ctrl[CTRL_ERR], ERR_CAP);
-        if constexpr (JOB) {
+        if constexpr (HANDED) {
             shared_store(Q.t + s, shared_load(Q.t + s) + c_tours);
+            if constexpr (PART) shared_store(Q.m + s, m);
         } else {
             Q.t[s] += c_tours;
             Q.m[s] = m;
@@ -1668,7 +1678,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     if (lane < STATS_WORDS) {
         // lane i: word i of the sequence's counters
         uint64_t* w = Q.stats + (size_t)s * STATS_WORDS + lane;
-        const uint64_t old = JOB ? shared_load(w) : *w;
+        const uint64_t old = HANDED ? shared_load(w) : *w;
         uint64_t c = old;
         c += lane == ST_STEPS ? (uint32_t)c_events - c_prunes : 0u;
         c += lane == ST_EVENTS ? c_events : 0ull;
@@ -1680,9 +1690,10 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         if (lane == ST_MAXDEPTH && c < c_maxd) c = c_maxd;
         if (lane == ST_DIGEST) c = digest;
         if (lane == ST_CAPPED && abort) c = 1;
-        if constexpr (JOB) shared_store(w, c);
+        if constexpr (HANDED) shared_store(w, c);
         else *w = c;
     }
+    if constexpr (PART) *left = abort ? 0u : cap - ((uint32_t)c_events - c_prunes);
     return c_tours | (abort ? WALK_ABORTED : 0u);
 }
 
@@ -1735,6 +1746,71 @@ __global__ void WAVES4 batch_kernel(BatchArgs B) { batch_body<false, false>(B); 
 __global__ void WAVES4 batch_obs_kernel(BatchArgs B) { batch_body<true, false>(B); }
 __global__ void WAVES4 batch_long_kernel(BatchArgs B) { batch_body<false, true>(B); }
 __global__ void WAVES4 batch_long_obs_kernel(BatchArgs B) { batch_body<true, true>(B); }
+
+// One problem whose sequences are more than the waves that run at once.  Their
+// steps differ several times over (a tour can be a thousand times longer than
+// most), so with whole sequences as work items the last long ones run on a chip
+// that has gone idle.  Here an item is a part of a sequence's tours: a wave takes
+// the sequences in turn for their first part, and puts a sequence back at the end
+// of a list for its next one.  All advance at the same pace, a slow one is never
+// left waiting for a start, and only single long tours are left at the end.
+// Every sequence enters the list parts - 1 times (also when its step cap has
+// stopped it), so each ticket past the first N gets an entry from a wave that is
+// running, and every wave ends at a ticket past the last.
+// Mean of six epochs, ms, whole sequences / in 2 / 4 / 8 / 16 parts:
+//   16384 cubic sequences of 1000 steps, 32 tours, 4096 waves  82.5 / 80.3 / 78.7 / 79.5 / 80.4
+//   4096 square sequences of 500 steps, 64 tours, 3072 waves   34.4 / 34.5 / 33.4 / 33.4 / 33.6
+// (the cubic steps alone at full rate: 45; the longest sequence alone: 38).
+template <bool LONG>
+__device__ __forceinline__ void part_body(const PartArgs& A) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int lane = (int)threadIdx.x;
+    const ProblemDesc P = load_const(A.desc);
+    SumRec* row = LONG ? A.wave_rows + (size_t)blockIdx.x * P.row : nullptr;
+    const uint32_t items = P.N * A.parts;
+    for (;;) {
+        uint32_t got = 0u;
+        if (lane == 0) got = atomicAdd(A.queue, 1u);
+        const uint32_t item = ufirst(__shfl(got, 0, 64));
+        if (item >= items) {
+            // (as in batch_body)
+            if (item - items == gridDim.x - 1u && lane == 0) *A.queue = 0u;
+            break;
+        }
+        uint32_t s = item, part = 0u, left = A.step_cap;
+        if (item >= P.N) {
+            uint64_t entry;
+            for (uint32_t naps = 1u;; naps = min(2u * naps, 4u)) {
+                entry = ufirst64(shared_load(A.list + 1 + (item - P.N)));
+                if (entry != 0ull) break;
+                for (uint32_t k = 0; k < naps; ++k) __builtin_amdgcn_s_sleep(127);
+            }
+            s = ((uint32_t)entry & (PART_MAX_N - 1u)) - 1u;
+            part = (uint32_t)entry / PART_MAX_N;
+            left = (uint32_t)(entry >> 32);
+        }
+        asm volatile("" ::: "memory");         // (nothing of the sequence is read before it is taken)
+        const uint32_t tours = min(A.part_tours, A.tours - part * A.part_tours);
+        if (left != 0u) {
+            if (P.dim == 2)
+                walk_sequence<2, false, LONG, false, false, true>(A.desc, tours, left, s, lds, P.G, row, &left);
+            else if (P.ckey)
+                walk_sequence<3, false, LONG, true, false, true>(A.desc, tours, left, s, lds, P.G, row, &left);
+            else
+                walk_sequence<3, false, LONG, false, false, true>(A.desc, tours, left, s, lds, P.G, row, &left);
+        }
+        if (part + 1u < A.parts) {
+            writes_arrived();
+            if (lane == 0) {
+                const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(A.list), 1ull);
+                shared_store(A.list + 1 + at, ((uint64_t)left << 32) | ((part + 1u) * PART_MAX_N + s + 1u));
+            }
+        }
+    }
+}
+
+__global__ void WAVES4 part_kernel(PartArgs A) { part_body<false>(A); }
+__global__ void WAVES4 part_long_kernel(PartArgs A) { part_body<true>(A); }
 
 // ---------------------------------------------------------------------------
 // Device-side epoch chaining.  Every problem runs its whole epoch schedule in
@@ -2347,6 +2423,12 @@ hipError_t launch_batch(const BatchArgs& b, uint32_t workgroups, uint32_t lds_by
     else if (long_walk) hipLaunchKernelGGL(batch_long_kernel, g, t, lds_bytes, s, b);
     else if (observables) hipLaunchKernelGGL(batch_obs_kernel, g, t, lds_bytes, s, b);
     else hipLaunchKernelGGL(batch_kernel, g, t, lds_bytes, s, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_parts(const PartArgs& a, uint32_t workgroups, uint32_t lds_bytes, hipStream_t s, bool long_walk) {
+    if (long_walk) hipLaunchKernelGGL(part_long_kernel, dim3(workgroups), dim3(64), lds_bytes, s, a);
+    else hipLaunchKernelGGL(part_kernel, dim3(workgroups), dim3(64), lds_bytes, s, a);
     return hipGetLastError();
 }
 
