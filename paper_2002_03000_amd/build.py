@@ -29,6 +29,10 @@ def build(verbose: bool = False, jobs: int = 2) -> str:
         cmd = ["hipcc", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
                "-ffp-contract=off", "-fno-fast-math",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               # loop heads at 32 bytes: where they fall otherwise moves a walk's step
+               # by 2% either way (256 Rosenbluth walks of 6000 cubic steps, twice:
+               # 1.93 ms, or 1.97 as it happens)
+               "-falign-loops=32",
                "-Wall", "-Wno-unused-function",
                "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
                "-c", src, "-o", obj]

@@ -854,6 +854,19 @@ __device__ __forceinline__ void write_site(uint32_t il, uint32_t taddr, uint64_t
                  :: "s"(il), "v"(taddr), "v"(key), "v"(saddr), "v"(slot) : "memory", "scc");
 }
 
+// The lanes where |x| < y, and where |x| > y, for the scalar unit (the compiler
+// would form |x| in registers for two compares).
+__device__ __forceinline__ uint64_t lanes_below(double x, double y) {
+    uint64_t m;
+    asm("v_cmp_lt_f64_e64 %0, |%1|, %2" : "=s"(m) : "v"(x), "s"(y));
+    return m;
+}
+__device__ __forceinline__ uint64_t lanes_above(double x, double y) {
+    uint64_t m;
+    asm("v_cmp_gt_f64_e64 %0, |%1|, %2" : "=s"(m) : "v"(x), "v"(y));
+    return m;
+}
+
 // The lowest bit set in m, or all ones for none.
 __device__ __forceinline__ uint32_t first_bit(uint64_t m) {
     uint32_t r;
@@ -967,12 +980,13 @@ __device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
 // blocks beside it / 71, with the scalar unit's waits filled and every value of
 // the walk that is the same in all lanes known to be so / 61, decided by the
 // hardware's reciprocal and a margin, the look-up first, the blocks beside it
-// without copies / with full walks stopped by a guard record:
-//   one square sequence of 20-step walks, 1000 tours     12.46 / 8.42 / 6.72 / 6.48 / 6.23 / 5.26
-//   4096 square sequences of 500 steps, 64 tours          94.6 / 70.2 / 47.6 / 46.5 / 42.3 / 41.6
-//   16384 cubic sequences of 1000 steps, 32 tours          198 /  149 /  101 / 98.9 / 86.8 / 86.3
-//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 3.40 / 2.15 / 1.97 / 1.96 / 1.94
-// A lone wave's step (us): square 0.625 -> 0.235, cubic 0.610 -> 0.213.
+// without copies / with full walks stopped by a guard record / the blocks beside
+// it without copies after a resume either (and, the two large ones, in parts):
+//   one square sequence of 20-step walks, 1000 tours     12.46 / 8.42 / 6.72 / 6.48 / 6.23 / 5.26 / 5.03
+//   4096 square sequences of 500 steps, 64 tours          94.6 / 70.2 / 47.6 / 46.5 / 42.3 / 41.6 / 38.6
+//   16384 cubic sequences of 1000 steps, 32 tours          198 /  149 /  101 / 98.9 / 86.8 / 86.3 / 81.4
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 3.40 / 2.15 / 1.97 / 1.96 / 1.94 / 1.93
+// A lone wave's step (us): square 0.625 -> 0.222, cubic 0.610 -> 0.205.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 // run_ahead's distance from a decision that the rounding of r could change: the
 // hardware's reciprocal is within 2^-24 and a uniform's high word within 2^-20.
@@ -1395,7 +1409,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     d += 128u;
                 } while (__ballot(end - sa > d) != 0ull);
             }
-            sp += min(rem - 1u, 1u) - 1u;      // its last copy: the entry is done
+            // (its last copy: the entry is done)
+            asm("s_cmp_eq_u32 %1, 1\n\ts_subb_u32 %0, %0, 0" : "+s"(sp) : "s"(rem) : "scc");
             no_decision();
             load_next();
         };
@@ -1425,6 +1440,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     li -= ~(uint32_t)trap;
                     resume(at);
                 }
+                // (or the product of weight and tours, which a resume forms too, is
+                // formed in both branches before here, and the state copied around)
+                if constexpr (decltype(decide)::value) asm volatile("" : "+v"(wm));
                 scan(decide, no{});
                 while (chosen()) {
                     commit(w1);
@@ -1439,8 +1457,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                     // (a ratio out of range or too near the uniform, a uniform that
                     // is not the event's or a sum out of range: no number passes;
                     // nor does a common decision, all places taken)
-                    sure = (__ballot(__builtin_fabs(r1) < 0.9375) &
-                            __ballot(__builtin_fabs(r1) > uu + 4.0 * DECISION_MARGIN) & plain) | trap;
+                    sure = (lanes_below(r1, 0.9375) & lanes_above(r1, uu + 4.0 * DECISION_MARGIN) & plain) | trap;
                     il2 = first_bit(pick);
                     ends = (uint32_t)(below1 | trap);
                     // two copies need a place for the grown one and one in the
