@@ -92,7 +92,7 @@ struct Shape {
 };
 
 // The occupancy table holds at most n_max + 1 sites; at least twice that many
-// slots keeps linear-probing runs short.  One walk per wavefront keeps the
+// slots keeps probing runs short and places free.  One walk per wavefront keeps the
 // sequence's per-length sums (and, with observables, its sums of W * R^2) in
 // LDS beside the table.  Where that does not
 // fit (walks of several thousand steps), or where PPERM_FLAG_SUMS_GLOBAL asks

@@ -113,7 +113,7 @@ struct BatchArgs {
     LaunchEntry single;           // count == 1
     uint32_t count;
     uint32_t total_items;
-    uint32_t* queue;              // zeroed before the launch
+    uint32_t* queue;              // zero before the launch, and after it
 };
 
 // A launch whose work items are parts of a sequence's tours (part_body).  list: a

@@ -12,7 +12,7 @@
 //     subtable o of the walk's table, so all neighbours are looked up in all
 //     their places in one LDS instruction and resolved with two wave ballots;
 //   - the random numbers: lane i computes the Philox4x32-10 block of event
-//     k0+i, so one pass of the (quarter-rate) multiplies serves 64 events;
+//     k0+i-1, so one pass of the multiplies serves 63 events;
 //   - the LIFO deletion of abandoned sites after a backtrack.
 // The walk's occupancy table (one key per site, restored exactly by LIFO
 // deletion through remembered slot ids), the slot ids and the sequence's own
@@ -585,16 +585,15 @@ __global__ void __launch_bounds__(64) run_kernel(RunArgs A) {
 // ---------------------------------------------------------------------------
 // Wave-per-walk growth kernel.  One 64-lane wavefront owns one walk, so every
 // quantity of the walk is uniform across the wave and every branch is a
-// scalar branch; the lanes only split the occupancy scan (lane = dir * W + off
-// reads probe position off of direction dir), the Philox blocks (lane i holds
-// the block of event kb + i, fetched with readlane) and the LIFO deletions.
+// scalar branch; the lanes only split the occupancy scan (lane = dir * W + o
+// reads neighbour dir's slot in subtable o), the Philox blocks (lane i holds
+// the block of event kb + i - 1, fetched with readlane) and the LIFO deletions.
 // The sequence's own per-length sums live in LDS while its tours run (no
-// global round trip on the record / decision path), the pooled sums are read
-// with scalar loads, and each pending-copy entry carries its endpoint site, so
-// a backtrack needs no table lookup to restore the walk's end.
+// global round trip on the record / decision path), the pooled sums are loaded
+// a step ahead, and each pending-copy entry carries its endpoint site, so a
+// backtrack needs no table lookup to restore the walk's end.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t ufirst(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int ufirst_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint64_t ufirst64(uint64_t v) {
     return ((uint64_t)ufirst((uint32_t)(v >> 32)) << 32) | (uint64_t)ufirst((uint32_t)v);
 }
@@ -611,10 +610,10 @@ __device__ __forceinline__ double lane_value(double v, uint32_t l) {
     return __builtin_bit_cast(double, lane_value(__builtin_bit_cast(uint64_t, v), l));
 }
 
-// Address-space views.  The pooled sums are never written while a growth
-// launch runs, so uniform reads of them may go through the constant space
-// (scalar loads, which do not wait on the LDS counter as flat loads do); the
-// copy stack is ordinary global memory.
+// Address-space views.  A problem's descriptor is never written while a growth
+// launch runs, so it is read through the constant space (scalar loads, whose
+// values the compiler knows to be the same in all lanes); sums and the copy
+// stack are ordinary global memory.
 template <typename T>
 __device__ __forceinline__ const __attribute__((address_space(4))) T* as_const(const T* p) {
     return (const __attribute__((address_space(4))) T*)p;
@@ -1837,7 +1836,7 @@ __global__ void WAVES4 part_long_kernel(PartArgs A) { part_body<true>(A); }
 // with zeros to p2 leaves -- as far as it is the second of two children to
 // arrive, adding its partner's partial row into the left child's row.  The
 // wave that completes the root adds the tree into the pooled sums (into a
-// fresh per-epoch copy, so that scalar loads of later epochs never meet a
+// fresh per-epoch copy, so that no load of a later epoch ever meets a
 // line cached before it was written), adds the epoch's tours to M and
 // publishes the next epoch.  The result is the same as run + merge per epoch.
 // ---------------------------------------------------------------------------
