@@ -18,6 +18,14 @@ HEADERS = [os.path.join(HERE, "csrc", "pperm_internal.h"), os.path.join(ROOT, "i
            os.path.join(ROOT, "include", "pperm_probe.h")]
 LIB = os.path.join(HERE, "libpperm.so")
 ARCH = os.environ.get("PPERM_OFFLOAD_ARCH", "gfx950")
+FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # loop heads at 32 bytes: where they fall otherwise moves a walk's step
+         # by 2% either way (256 Rosenbluth walks of 6000 cubic steps, twice:
+         # 1.93 ms, or 1.97 as it happens)
+         "-falign-loops=32",
+         "-Wall", "-Wno-unused-function",
+         "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
 
 
 def build(verbose: bool = False, jobs: int = 2) -> str:
@@ -26,15 +34,7 @@ def build(verbose: bool = False, jobs: int = 2) -> str:
     for src in SOURCES:
         obj = os.path.join(HERE, "_build", os.path.basename(src) + ".o")
         os.makedirs(os.path.dirname(obj), exist_ok=True)
-        cmd = ["hipcc", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
-               "-ffp-contract=off", "-fno-fast-math",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-               # loop heads at 32 bytes: where they fall otherwise moves a walk's step
-               # by 2% either way (256 Rosenbluth walks of 6000 cubic steps, twice:
-               # 1.93 ms, or 1.97 as it happens)
-               "-falign-loops=32",
-               "-Wall", "-Wno-unused-function",
-               "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
+        cmd = ["hipcc", f"--offload-arch={ARCH}", *FLAGS,
                "-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)

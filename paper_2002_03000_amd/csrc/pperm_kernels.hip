@@ -875,20 +875,46 @@ __device__ __forceinline__ uint32_t first_bit(uint64_t m) {
 
 // Empties the slots at LDS addresses `at` of the lanes whose `index` is below
 // `depth` (a vector compare that selects the lanes itself: through a saved mask
-// the scalar unit would wait for it).
+// the scalar unit would wait for it).  A lane read must be four wait states behind
+// a vector instruction that writes the lane mask, which the compiler does not see
+// in here; this form waits for them.
 template <typename Key>
 __device__ __forceinline__ void clear_sites(uint32_t index, uint32_t depth, uint32_t at) {
     const Key zero = 0;
     if constexpr (sizeof(Key) == 8)
         asm volatile("v_cmpx_lt_u32_e32 %0, %1\n\t"
                      "ds_write_b64 %2, %3\n\t"
-                     "s_mov_b64 exec, -1"
+                     "s_mov_b64 exec, -1\n\t"
+                     "s_nop 1"
                      :: "v"(index), "v"(depth), "v"(at), "v"(zero) : "memory", "vcc");
     else
         asm volatile("v_cmpx_lt_u32_e32 %0, %1\n\t"
                      "ds_write_b32 %2, %3\n\t"
-                     "s_mov_b64 exec, -1"
+                     "s_mov_b64 exec, -1\n\t"
+                     "s_nop 1"
                      :: "v"(index), "v"(depth), "v"(at), "v"(zero) : "memory", "vcc");
+}
+
+// The same, and one copy less to resume in lane p mod 64 of `rem` (which fills the
+// wait states).
+template <typename Key>
+__device__ __forceinline__ void clear_sites_take_copy(uint32_t index, uint32_t depth, uint32_t at, uint32_t& rem,
+                                                      uint32_t p) {
+    const Key zero = 0;
+    if constexpr (sizeof(Key) == 8)
+        asm volatile("v_cmpx_lt_u32_e32 %1, %2\n\t"
+                     "ds_write_b64 %3, %4\n\t"
+                     "s_lshl_b64 exec, 1, %5\n\t"
+                     "v_add_u32 %0, -1, %0\n\t"
+                     "s_mov_b64 exec, -1"
+                     : "+v"(rem) : "v"(index), "v"(depth), "v"(at), "v"(zero), "s"(p) : "memory", "vcc", "scc");
+    else
+        asm volatile("v_cmpx_lt_u32_e32 %1, %2\n\t"
+                     "ds_write_b32 %3, %4\n\t"
+                     "s_lshl_b64 exec, 1, %5\n\t"
+                     "v_add_u32 %0, -1, %0\n\t"
+                     "s_mov_b64 exec, -1"
+                     : "+v"(rem) : "v"(index), "v"(depth), "v"(at), "v"(zero), "s"(p) : "memory", "vcc", "scc");
 }
 
 // The copy stack's registers: one pending entry per lane.
@@ -937,15 +963,6 @@ __device__ __forceinline__ void put_entry(CopyLanes<Key>& c, uint32_t p, uint32_
                      : "scc");
     }
     c.m = __builtin_bit_cast(double, ((uint64_t)mhi << 32) | mlo);
-}
-
-// One copy less to resume in lane p mod 64.
-template <typename Key>
-__device__ __forceinline__ void take_copy(CopyLanes<Key>& c, uint32_t p) {
-    asm volatile("s_lshl_b64 exec, 1, %1\n\t"
-                 "v_add_u32 %0, -1, %0\n\t"
-                 "s_mov_b64 exec, -1"
-                 : "+v"(c.rem) : "s"(p) : "scc");
 }
 
 // One sequence's `tours` tours against frozen pooled sums (the whole hot path
@@ -1395,11 +1412,10 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             ekey = lane_value(cs.key, tl);
             ra = lane_value(cs.ra, tl) + vz;
             const uint32_t rem = lane_value(cs.rem, tl);
-            take_copy(cs, tl);
             // LIFO deletion of the sites after it restores the table exactly
             const uint32_t end = sa;
             sa = (ra >> 3) + (sid_base - rec_base / 8u);
-            clear_sites<Key>(lane2, end - sa, at * (uint32_t)sizeof(Key));
+            clear_sites_take_copy<Key>(lane2, end - sa, at * (uint32_t)sizeof(Key), cs.rem, tl);
             if (__builtin_expect(__ballot(end - sa > 128u) != 0ull, 0)) {
                 uint32_t d = 128u;
                 do {
