@@ -22,6 +22,10 @@ enum : uint32_t { CTRL_QUEUE = 0, CTRL_ERR = 1, CTRL_WORDS = 16 };
 // Modes (same values as the ABI).
 enum : uint32_t { MODE_SHARED = 0, MODE_INDEPENDENT = 1, MODE_ROSENBLUTH = 2 };
 
+// The row of the pooled sums, counts and tours that sequence s reads: its own in
+// Algorithm 1, else the only one.
+constexpr uint32_t pooled_row(uint32_t mode, uint32_t s) { return mode == MODE_INDEPENDENT ? s : 0u; }
+
 // Cubic walks up to COMPACT3_MAX_N steps key a site (x, y, z) in 32 bits as
 // x + SITE3_Y y + SITE3_Z z + SITE3_0 (see Site3c, where the limit comes from).
 constexpr uint32_t COMPACT3_MAX_N = 2063;

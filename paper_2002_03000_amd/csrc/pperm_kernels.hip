@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(64) run_kernel(RunArgs A) {
     uint64_t t = 0, tt = 0;
     SumRec rec0 = {0.0, 0, 0u};           // L[s][0]: one record per tour
     const SumRec* Grow = A.G;
-    uint64_t MGs = shared_mode ? A.MG[0] : 0;
+    uint64_t MGs = 0;
     uint64_t st_steps = 0, st_events = 0, st_enrich = 0, st_copies = 0, st_prunes = 0,
              st_traps = 0, st_tours = 0, st_maxd = 0, st_digest = 0, st_capped = 0;
     uint32_t steps_call = 0;
@@ -340,10 +340,8 @@ __global__ void __launch_bounds__(64) run_kernel(RunArgs A) {
                 st_copies = sr[ST_COPIES]; st_prunes = sr[ST_PRUNES]; st_traps = sr[ST_TRAPS];
                 st_tours = sr[ST_TOURS]; st_maxd = sr[ST_MAXDEPTH]; st_digest = sr[ST_DIGEST];
                 st_capped = sr[ST_CAPPED];
-                if (!shared_mode) {
-                    Grow = A.G + rb0;
-                    MGs = A.MG[s];
-                }
+                Grow = A.G + (size_t)pooled_row(A.mode, s) * row;
+                MGs = A.MG[pooled_row(A.mode, s)];
                 tours_left = A.tours;
                 steps_call = 0;
                 phase = PH_NEED_TOUR;
@@ -1108,12 +1106,10 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
 
     // the copy stack of sequence s
     StackEntry* stk = P.stack + (size_t)(PART ? blockIdx.x : s) * n_max;
-    uint64_t MGs = 0ull;
-    if (shared_mode) MGs = JOB ? ufirst64(shared_load(P.MG)) : P.MG[0];
-
     const size_t rb0 = (size_t)s * row;
-    const SumRec* Grow = shared_mode ? Gsrc : Gsrc + rb0;
-    if (!shared_mode) MGs = ufirst64(P.MG[s]);
+    const uint32_t grow = pooled_row(P.mode, s);
+    const SumRec* Grow = Gsrc + (size_t)grow * row;
+    const uint64_t MGs = ufirst64(JOB ? shared_load(P.MG) : P.MG[grow]);
     uint32_t tlo = ufirst((uint32_t)(HANDED ? shared_load(P.t + s) : P.t[s]));   // tour index: its low word keys the random numbers
     uint32_t m = JOB ? 0u : ufirst(PART ? shared_load(P.m + s) : P.m[s]);
     if constexpr (JOB) {
@@ -1506,7 +1502,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 Lm = ldexp(Lm, we - w.e);
                 weigh(w);
                 // (scan has moved on to the next length's sum)
-                if (__ballot(Lm != 0.0) != 0ull) G = pooled(ra, 0u);
+                if (control_mode && __ballot(Lm != 0.0) != 0ull) G = pooled(ra, 0u);
                 else no_decision();
                 arm(n);
                 continue;
