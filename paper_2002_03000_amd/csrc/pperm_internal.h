@@ -36,6 +36,9 @@ constexpr int STATS_WORDS = 10;
 constexpr uint32_t GROUPS = 16;   // sequence groups of the error estimate (s mod 16)
 enum : int { ST_STEPS = 0, ST_EVENTS, ST_ENRICH, ST_COPIES, ST_PRUNES, ST_TRAPS,
              ST_TOURS, ST_MAXDEPTH, ST_DIGEST, ST_CAPPED };
+// Whether 32-bit word k of the statistics is the low word of a sequence's digest
+// (in 64 bits: 2^32 words are 214,748,364.8 sequences).
+constexpr bool is_digest_word(uint64_t k) { return k % (2u * STATS_WORDS) == 2u * ST_DIGEST; }
 
 // 16-byte record of an extended-range sum: value = m * 2^e (m in [0.5, 1) or
 // m = 0 and e = 0) and, for the per-sequence sums, the sample count h.

@@ -2398,7 +2398,7 @@ __global__ void __launch_bounds__(256) init_state_kernel(uint32_t* zero, size_t 
          i += (size_t)gridDim.x * 256) {
         if (i - desc0 < sizeof(ProblemDesc) / 4) continue;      // (inside the range)
         const size_t k = i - stats0;
-        const bool digest = k < stats_words && (uint32_t)k % (2u * STATS_WORDS) == 2u * ST_DIGEST;
+        const bool digest = k < stats_words && is_digest_word(k);
         zero[i] = digest ? FNV_OFFSET : 0u;
     }
     if (blockIdx.x == 0u && threadIdx.x == 0u) *desc = d;

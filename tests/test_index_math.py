@@ -15,11 +15,14 @@ def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("index")
     (d / "w.cpp").write_text(
         '#include "pperm_internal.h"\n'
-        'extern "C" uint32_t row_of(uint32_t mode, uint32_t s) { return pperm::pooled_row(mode, s); }\n')
+        'extern "C" uint32_t row_of(uint32_t mode, uint32_t s) { return pperm::pooled_row(mode, s); }\n'
+        'extern "C" bool digest_word(uint64_t k) { return pperm::is_digest_word(k); }\n')
     subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
                     "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "paper_2002_03000_amd", "csrc"),
                     str(d / "w.cpp"), "-o", str(d / "w.so")], check=True, timeout=120)
-    return ctypes.CDLL(str(d / "w.so"))
+    lib = ctypes.CDLL(str(d / "w.so"))
+    lib.digest_word.argtypes, lib.digest_word.restype = [ctypes.c_uint64], ctypes.c_bool
+    return lib
 
 
 @pytest.mark.parametrize("mode,rows", [(SHARED, 1), (INDEPENDENT, 4096), (ROSENBLUTH, 1)])
@@ -27,3 +30,10 @@ def test_pooled_rows_lie_in_the_pooled_sums(lib, mode, rows):
     # (a chained launch keeps such a row per epoch, with nothing after the last)
     for s in (0, 1, 16, 4095):
         assert lib.row_of(mode, s) == (s if rows > 1 else 0) < rows
+
+
+def test_a_new_context_seeds_the_digest_of_every_sequence(lib):
+    # ten 64-bit counters a sequence, the digest the ninth; word 2^32 of the
+    # statistics belongs to sequence 214,748,364
+    for s in (0, 1, 214748363, 214748364, 214748365, 429496729, 2 ** 32 - 1):
+        assert [w for w in range(20) if lib.digest_word(20 * s + w)] == [16], s
