@@ -375,16 +375,23 @@ int pperm_create(const pperm_config* cfg, void* d_workspace, size_t bytes, void*
 }
 
 // Whether the tours of one call go out as parts of sequences (part_body), and how:
-// where more sequences than fit at once have enough steps each.  A part is a
-// quarter of the tours, or more where that is under 2048 steps (about 0.5 ms; a
-// hand-over takes some 20 us), its list lies in the merge's scratch, which a run does
-// not use, and the rows of long walks in the stacks of the sequences past the
-// first `workgroups` (a stack belongs to a wave here, not to a sequence).
+// where more sequences than fit at once have at least two parts each (part_tours).
+// The list of parts lies in the merge's scratch, which a run does not use, and the
+// rows of long walks in the stacks of the sequences past the first `workgroups` (a
+// stack belongs to a wave here, not to a sequence).  Just above the number of waves
+// parts neither gain nor lose: time of whole sequences over time in parts, at 1.02 /
+// 1.3 / 2 / 3 times as many sequences as waves, parts of about 4000 steps (runs
+// differ by 1 to 4%):
+//   square, 60 steps    1.01 / 1.04 / 1.11 / 1.08
+//   square, 127 steps   0.99 / 1.01 / 1.08 / 1.12
+//   square, 500 steps   1.01 / 1.03 / 1.03 / 1.07
+//   cubic, 250 steps    1.01 / 1.01 / 1.04 / 1.08
+//   cubic, 1000 steps   0.99 / 0.97 / 0.99 / 0.97   (16384 of them, 32 tours: 1.05)
 static bool plan_parts(pperm_ctx* x, uint32_t tours, PartArgs* a) {
-    const uint64_t N = x->cfg.n_sequences, n1 = x->cfg.n_max + 1ull, wgs = x->workgroups;
+    const uint64_t N = x->cfg.n_sequences, wgs = x->workgroups;
     if (N <= wgs || N >= PART_MAX_N - 1u || (x->cfg.flags & PPERM_FLAG_OBSERVABLES)) return false;
     const uint64_t room = x->lay.total - x->lay.scratch;
-    uint64_t part = std::max<uint64_t>((tours + PART_MAX - 1ull) / PART_MAX, (2048ull + n1 - 1ull) / n1), parts;
+    uint64_t part = part_tours(x->cfg.dim, x->cfg.mode, x->cfg.n_max, tours), parts;
     for (;; part *= 2ull) {
         parts = (tours + part - 1ull) / part;
         if (parts < 2ull) return false;

@@ -128,6 +128,25 @@ struct BatchArgs {
 // zero before the launch: the rest of the step cap (32 bits), the part, and the
 // sequence plus one (in PART_MAX_N).
 constexpr uint32_t PART_MAX_N = 1u << 26, PART_MAX = 4;
+
+// Steps a tour takes on average: one sample a length where the histogram is flat;
+// a Rosenbluth walk goes on until it is trapped, after 71 steps on the square and
+// some 3950 on the cubic lattice, or has n_max.
+constexpr uint64_t tour_steps(uint32_t dim, uint32_t mode, uint32_t n_max) {
+    const uint64_t full = n_max + 1ull, trapped = dim == 2u ? 71ull : 3950ull;
+    return mode == MODE_ROSENBLUTH && full > trapped ? trapped : full;
+}
+
+// Tours of a part: a quarter of the call's, or more where that is under 2048 steps
+// (about 0.5 ms; a hand-over takes some 20 us and, in a long row, more: square
+// Rosenbluth walks of up to 2000 steps, 4400 sequences of 8 tours on 2048 waves,
+// take 0.74 ms in parts of 142 steps and 0.41 ms whole).
+constexpr uint64_t part_tours(uint32_t dim, uint32_t mode, uint32_t n_max, uint32_t tours) {
+    const uint64_t steps = tour_steps(dim, mode, n_max);
+    const uint64_t quarter = (tours + PART_MAX - 1ull) / PART_MAX, least = (2048ull + steps - 1ull) / steps;
+    return quarter > least ? quarter : least;
+}
+
 struct PartArgs {
     const ProblemDesc* desc;
     uint32_t* queue;

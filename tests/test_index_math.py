@@ -16,12 +16,15 @@ def lib(tmp_path_factory):
     (d / "w.cpp").write_text(
         '#include "pperm_internal.h"\n'
         'extern "C" uint32_t row_of(uint32_t mode, uint32_t s) { return pperm::pooled_row(mode, s); }\n'
-        'extern "C" bool digest_word(uint64_t k) { return pperm::is_digest_word(k); }\n')
+        'extern "C" bool digest_word(uint64_t k) { return pperm::is_digest_word(k); }\n'
+        'extern "C" uint64_t part(uint32_t dim, uint32_t mode, uint32_t n, uint32_t T)'
+        ' { return pperm::part_tours(dim, mode, n, T); }\n')
     subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
                     "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "paper_2002_03000_amd", "csrc"),
                     str(d / "w.cpp"), "-o", str(d / "w.so")], check=True, timeout=120)
     lib = ctypes.CDLL(str(d / "w.so"))
     lib.digest_word.argtypes, lib.digest_word.restype = [ctypes.c_uint64], ctypes.c_bool
+    lib.part.restype = ctypes.c_uint64
     return lib
 
 
@@ -37,3 +40,14 @@ def test_a_new_context_seeds_the_digest_of_every_sequence(lib):
     # statistics belongs to sequence 214,748,364
     for s in (0, 1, 214748363, 214748364, 214748365, 429496729, 2 ** 32 - 1):
         assert [w for w in range(20) if lib.digest_word(20 * s + w)] == [16], s
+
+
+@pytest.mark.parametrize("dim,mode,n_max,tours,part", [
+    (2, SHARED, 500, 64, 16), (3, SHARED, 1000, 32, 8), (2, SHARED, 127, 33, 16), (2, SHARED, 1, 4096, 1024),
+    (3, INDEPENDENT, 255, 17, 8),
+    # a trapped walk's steps, not n_max: 2048 / 71 = 28.8, and 2048 / 3950 < 1
+    (2, ROSENBLUTH, 2000, 8, 29), (2, ROSENBLUTH, 500, 200, 50), (2, ROSENBLUTH, 60, 8, 34),
+    (3, ROSENBLUTH, 700, 9, 3), (3, ROSENBLUTH, 9000, 3, 1),
+])
+def test_a_part_has_a_quarter_of_the_tours_or_2048_steps(lib, dim, mode, n_max, tours, part):
+    assert lib.part(dim, mode, n_max, tours) == part
