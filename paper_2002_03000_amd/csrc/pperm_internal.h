@@ -128,6 +128,7 @@ struct BatchArgs {
 // zero before the launch: the rest of the step cap (32 bits), the part, and the
 // sequence plus one (in PART_MAX_N).
 constexpr uint32_t PART_MAX_N = 1u << 26, PART_MAX = 4;
+static_assert((uint64_t)PART_MAX * PART_MAX_N <= 1ull << 32, "an entry's part");
 
 // Steps a tour takes on average: one sample a length where the histogram is flat;
 // a Rosenbluth walk goes on until it is trapped, after 71 steps on the square and
@@ -143,7 +144,7 @@ constexpr uint64_t tour_steps(uint32_t dim, uint32_t mode, uint32_t n_max) {
 // take 0.74 ms in parts of 142 steps and 0.41 ms whole).
 constexpr uint64_t part_tours(uint32_t dim, uint32_t mode, uint32_t n_max, uint32_t tours) {
     const uint64_t steps = tour_steps(dim, mode, n_max);
-    const uint64_t quarter = (tours + PART_MAX - 1ull) / PART_MAX, least = (2048ull + steps - 1ull) / steps;
+    const uint64_t quarter = ((uint64_t)tours + PART_MAX - 1u) / PART_MAX, least = (2048ull + steps - 1ull) / steps;
     return quarter > least ? quarter : least;
 }
 

@@ -48,6 +48,8 @@ def test_a_new_context_seeds_the_digest_of_every_sequence(lib):
     # a trapped walk's steps, not n_max: 2048 / 71 = 28.8, and 2048 / 3950 < 1
     (2, ROSENBLUTH, 2000, 8, 29), (2, ROSENBLUTH, 500, 200, 50), (2, ROSENBLUTH, 60, 8, 34),
     (3, ROSENBLUTH, 700, 9, 3), (3, ROSENBLUTH, 9000, 3, 1),
+    # as many tours as a call may ask for
+    (3, INDEPENDENT, 2, 2 ** 32 - 1, 2 ** 30), (2, ROSENBLUTH, 5000, 2 ** 32 - 4, 2 ** 30 - 1),
 ])
 def test_a_part_has_a_quarter_of_the_tours_or_2048_steps(lib, dim, mode, n_max, tours, part):
     assert lib.part(dim, mode, n_max, tours) == part
