@@ -102,6 +102,17 @@ def issue_fraction(steps_per_s, kernel, workload, probes):
             "per_simd_cycle": ach / hz, "peak_mixed_per_simd_cycle": probes["mixed_instr_per_s"] / hz}
 
 
+def growth_kernel(n_sequences, n_max, tours, shape, long_walk):
+    """The kernel that grows the walks of an epoch of `tours` (not of the first
+    epochs, which may be too short for parts): whole sequences, or parts of them
+    where they outnumber the waves of the launch and have two parts or more."""
+    if shape["walks_per_wave"] > 1:
+        return "run_kernel"
+    part = max(-(-tours // 4), -(-2048 // (n_max + 1)))
+    parts = n_sequences > shape["workgroups"] and tours > part
+    return ("part" if parts else "batch") + ("_long_kernel" if long_walk else "_kernel")
+
+
 def kernel_code_digest():
     """sha256 of the kernel source with comments and blank lines removed: the
     key under which counter summaries stay valid."""
@@ -358,7 +369,8 @@ def main():
     est_top = np.array([r[0][p.n_max] for r in results])
     rel_err = float(np.std(np.exp(est_top - est_top.mean()), ddof=1)) if len(results) > 1 else None
 
-    kernel = "batch_long_kernel" if (args.workload == "long2d" or args.sums_global) else "batch_kernel"
+    kernel = growth_kernel(p.n_sequences, p.n_max, p.tours_per_epoch, shape,
+                           args.workload == "long2d" or args.sums_global)
     probes = None if args.no_probe else probe_ceilings()
     line = {
         "metric": METRIC,
