@@ -36,8 +36,8 @@ ALG_OPS_PER_STEP = {2: 100 + 7 * 3 + 15 + 15 + 6, 3: 100 + 7 * 5 + 15 + 15 + 6}
 def lds_bytes_per_step(dim, n_max):
     """Algorithmic LDS bytes per walk-step: 2d - 1 occupancy-key reads and one
     insert of the packed key (4 bytes on the square lattice and, up to
-    n_max = 1023, on the cubic one; 8 bytes for longer cubic walks)."""
-    key = 4 if (dim == 2 or n_max <= 1023) else 8
+    n_max = 2063, on the cubic one; 8 bytes for longer cubic walks)."""
+    key = 4 if (dim == 2 or n_max <= 2063) else 8
     return 2 * dim * key
 # Algorithmic L2 bytes per walk-step: the pooled sum of the length read (8),
 # and where the sequence's sums live in global memory also its sum read and

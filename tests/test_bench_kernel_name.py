@@ -37,3 +37,11 @@ def test_growth_kernel(bench, p, workgroups, long_walk, kernel):
 def test_summaries_are_found_under_the_kernel_name(bench, summary):
     for kind in ("kernel_trace", "sq_counters", "traffic"):
         assert os.path.exists(os.path.join(bench.PROFILES, f"{summary}_{kind}.md"))
+
+
+def test_bytes_per_step_follow_the_key_format(bench):
+    import re
+    src = open(os.path.join(ROOT, "paper_2002_03000_amd", "csrc", "pperm_internal.h")).read()
+    last = int(re.search(r"COMPACT3_MAX_N = (\d+);", src).group(1))
+    assert [bench.lds_bytes_per_step(3, n) for n in (1, last, last + 1)] == [24, 24, 48]
+    assert bench.lds_bytes_per_step(2, last + 1) == 16
