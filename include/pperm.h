@@ -89,8 +89,7 @@ typedef struct pperm_config {
 /* Launch tuning: keep each sequence's per-length sums in its global row even
  * where they would fit in LDS beside the occupancy table.  Less LDS per walk
  * lets more walks share a compute unit, at the cost of a global read per
- * step; results never change.  Needs one walk per wavefront; such contexts
- * run through pperm_run_tours / pperm_merge_epoch (and their graphs) only. */
+ * step; results never change.  Needs one walk per wavefront. */
 #define PPERM_FLAG_SUMS_GLOBAL  4u
 
 /* Per-sequence counters, cumulative over the context's life (10 x uint64 each). */
@@ -235,9 +234,8 @@ int pperm_job_workspace_bytes(pperm_ctx* const* ctxs, const uint32_t* epochs, si
  * must be ordered after all earlier work of the contexts.  d_workspace:
  * caller-owned device memory of pperm_job_workspace_bytes, 256-byte aligned.
  * Errors: EINVAL (bad arguments, a zero entry in a schedule, a context twice,
- * another device, PPERM_INDEPENDENT mode, several walks per wave, observables,
- * per-length sums in global memory), ESTATE (a context with unmerged tours),
- * EOVERFLOW, EDEVICE. */
+ * another device, PPERM_INDEPENDENT mode, several walks per wave,
+ * observables), ESTATE (a context with unmerged tours), EOVERFLOW, EDEVICE. */
 int pperm_run_job(pperm_ctx* const* ctxs, const uint32_t* const* schedules, const uint32_t* epochs,
                   size_t count, void* d_workspace, size_t bytes, void* hip_stream);
 
@@ -273,7 +271,8 @@ int pperm_run_job_sliced(pperm_ctx* const* ctxs, const uint32_t* const* schedule
                          const pperm_job_limits* limits, uint32_t slice_us, uint32_t* epochs_done,
                          uint32_t* stop, double* rel_err);
 
-/* Synchronise the stream and read the merged state into caller-owned host
+/* Synchronise the context's stream, and the default stream with the streams that
+ * order with it, and read the merged state into caller-owned host
  * buffers of `len` >= n_max + 1 entries:
  *   log_cn[n] = log of the estimate of c_n (eqn (4); the mean of eqn (7) in
  *               PPERM_INDEPENDENT mode), -inf where no sample reached n;

@@ -247,7 +247,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t job_occupancy(uint32_t lds_bytes, int* blocks_per_cu);
 
 // True for a valid configuration whose walks run with their per-length sums
-// in global memory (one problem per launch only).
+// in global memory.
 bool config_long_walk(const pperm_config* c);
 
 hipError_t launch_batch(const BatchArgs& b, uint32_t workgroups, uint32_t lds_bytes, hipStream_t s,

@@ -989,21 +989,17 @@ __device__ __forceinline__ void put_entry(CopyLanes<Key>& c, uint32_t p, uint32_
 // (run_ahead); enrichment to two copies, pruning and trapping (a quarter of the
 // square lattice's events) are short blocks beside it; and everything else is
 // handled outside, in the extended-range form (the event loop).
-// Measured (ms): with every case decided in line, 255 instructions and 17
-// branches a step / the straight block alone, 87 instructions / 78, with the
-// blocks beside it / 71, with the scalar unit's waits filled and every value of
-// the walk that is the same in all lanes known to be so / 61, decided by the
-// hardware's reciprocal and a margin, the look-up first, the blocks beside it
-// without copies / with full walks stopped by a guard record / the blocks beside
-// it without copies after a resume either (and, the two large ones, in parts):
-//   one square sequence of 20-step walks, 1000 tours     12.46 / 8.42 / 6.72 / 6.48 / 6.23 / 5.26 / 5.03
-//   4096 square sequences of 500 steps, 64 tours          94.6 / 70.2 / 47.6 / 46.5 / 42.3 / 41.6 / 38.6
-//   16384 cubic sequences of 1000 steps, 32 tours          198 /  149 /  101 / 98.9 / 86.8 / 86.3 / 81.4
-//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 3.40 / 2.15 / 1.97 / 1.96 / 1.94 / 1.93
-// A lone wave's step (us): square 0.625 -> 0.222, cubic 0.610 -> 0.205.
+// Measured with every case decided in line (255 instructions and 17 branches a
+// step) / now, ms, means of three seeds:
+//   one square sequence of 20-step walks, 1000 tours      12.4 / 5.02
+//   4096 square sequences of 500 steps, 64 tours          77.3 / 28.8
+//   16384 cubic sequences of 1000 steps, 32 tours          163 / 68.8
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.42 / 1.93
+// A lone wave's step (us): square 0.625 / 0.222, cubic 0.610 / 0.205.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 // run_ahead's distance from a decision that the rounding of r could change: the
-// hardware's reciprocal is within 2^-24 and a uniform's high word within 2^-20.
+// hardware's reciprocal has a stated error of 2^29 units in the last place (2^-23),
+// and a uniform's high word is within 2^-20.
 constexpr double DECISION_MARGIN = 0x1p-16;
 
 template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false, bool PART = false>
@@ -1328,9 +1324,10 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             const uint32_t x = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)hits, j));
             pick = __ballot(((x ^ (uint32_t)pdir) | S_::mark(v)) == 0u);
-            // (the term that takes the next sum from 1 - u is below its last
-            // place unless the sum is 2^440 times the weight or more, which
-            // stops here)
+            // (the term that takes the next sum from 1 - u leaves it as it is
+            // while it is below a quarter of its last place: for 1 - u of 2^-7
+            // or more, sums up to 2^440 * 2^we.  Beyond, the event is decided
+            // outside, with the same result)
             ut = __builtin_fma(t, small, uu);
             const uint64_t ok = __ballot(__builtin_fabs(r1) < ut);
             __builtin_amdgcn_sched_barrier(0);
