@@ -172,7 +172,7 @@ void compute_layout(const pperm_config* c, pperm_layout* L) {
     resolve_shape(c, &sh);
     // one copy stack per sequence (a sequence runs on one wavefront at a time)
     const uint64_t stack_slots = align_up(N, sh.walks_per_wave);
-    const uint64_t chunks = (N + 63) / 64;          // (more than a merge of MERGE_ROWS rows a block needs)
+    const uint64_t chunks = (N + 63) / 64;          // (blocks of a merge pass, at most)
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) {
         uint64_t o = off;
@@ -501,8 +501,8 @@ int pperm_merge_epoch(pperm_ctx* x) {
         x->open_tours = 0;
         return PPERM_OK;
     }
-    // aligned pairwise tree over sequences, MERGE_ROWS rows per block and pass
-    const uint64_t chunks = (N + MERGE_ROWS - 1) / MERGE_ROWS;
+    // aligned pairwise tree over sequences, merge_block rows per block and pass
+    const uint64_t chunks = ((uint64_t)N + 63) / 64;
     SumRec* bufd[2] = {at<SumRec>(x, x->lay.scratch), at<SumRec>(x, x->lay.scratch) + chunks * row};
     uint64_t* bufh[2] = {reinterpret_cast<uint64_t*>(bufd[1] + chunks * row),
                          reinterpret_cast<uint64_t*>(bufd[1] + chunks * row) + chunks * row};
@@ -517,7 +517,8 @@ int pperm_merge_epoch(pperm_ctx* x) {
     a.ncols = x->cfg.n_max + 1;
     int cur = 0;
     for (;;) {
-        const bool final_pass = (a.rows <= MERGE_ROWS);
+        a.block = merge_block(a.rows, a.ncols, a.zero != nullptr);
+        const bool final_pass = (a.rows <= a.block);
         a.out = final_pass ? G : bufd[cur];
         a.hout = final_pass ? HG : bufh[cur];
         a.accumulate = final_pass ? 1u : 0u;
@@ -527,7 +528,7 @@ int pperm_merge_epoch(pperm_ctx* x) {
         a.hin = bufh[cur];
         a.zero = nullptr;
         a.m = nullptr;
-        a.rows = (a.rows + MERGE_ROWS - 1) / MERGE_ROWS;
+        a.rows = (a.rows + a.block - 1) / a.block;
         cur ^= 1;
     }
     if (x->cfg.flags & PPERM_FLAG_OBSERVABLES) {
@@ -539,7 +540,8 @@ int pperm_merge_epoch(pperm_ctx* x) {
         a.m = nullptr;
         a.rows = N;
         for (;;) {
-            const bool final_pass = (a.rows <= MERGE_ROWS);
+            a.block = merge_block(a.rows, a.ncols, a.zero != nullptr);
+            const bool final_pass = (a.rows <= a.block);
             a.out = final_pass ? at<SumRec>(x, x->lay.obs_G) : bufd[cur];
             a.hout = nullptr;
             a.accumulate = final_pass ? 1u : 0u;
@@ -547,7 +549,7 @@ int pperm_merge_epoch(pperm_ctx* x) {
             if (final_pass) break;
             a.in = bufd[cur];
             a.zero = nullptr;
-            a.rows = (a.rows + MERGE_ROWS - 1) / MERGE_ROWS;
+            a.rows = (a.rows + a.block - 1) / a.block;
             cur ^= 1;
         }
     }

@@ -156,17 +156,41 @@ struct PartArgs {
     uint32_t tours, part_tours, parts, step_cap;
 };
 
-constexpr uint32_t MERGE_ROWS = 1024;   // rows of one block of a merge pass
+// Rows that a block of a merge pass takes: a power of two from 64 to MERGE_ROWS; the
+// pass is the last one where that is all of them.  A large block saves a pass, but
+// all of its waves wait for each other, and few blocks leave the chip idle.  us per
+// merge, with first blocks of 1024 rows / of 64 / as chosen here:
+//   1000 sequences of 50 steps     21.9 / 15.2 / 15.2
+//   4096                           30.8 / 17.2 / 17.2
+//   8192                           32.1 / 22.2 / 21.2
+//   1000 sequences of 1000 steps   24.3 / 27.8 / 24.3
+//   4096                             72 /   75 /   64
+//   16384                           222 /  205 /  162
+constexpr uint32_t MERGE_ROWS = 1024;
+constexpr uint32_t merge_block(uint32_t rows, uint32_t ncols, bool first) {
+    // one block: up to 512 rows, or up to 1024 where there are columns enough to fill
+    // the chip, or where the rows are sums of others already
+    if (rows <= 512u || (rows <= MERGE_ROWS && (!first || ncols > 512u))) return MERGE_ROWS;
+    // two passes, not three
+    if (rows > 512u * MERGE_ROWS) return MERGE_ROWS;
+    // many records: their reading counts, not the second pass
+    if ((uint64_t)rows * ncols >= 3u << 19) return 512u;
+    // few: one wave's rows are left for the second pass
+    uint32_t block = 64u;
+    while (block < 512u && 64u * block < rows) block *= 2u;
+    return block;
+}
 
 struct MergeArgs {
     const SumRec* in;      // [rows][row]
-    SumRec* out;           // [ceil(rows/MERGE_ROWS)][row], or G when final
+    SumRec* out;           // [ceil(rows/block)][row], or G when final
     uint64_t* hout;        // the same shape, or HG when final; nullptr: no counts
     const uint64_t* hin;   // later passes: [rows][row]; first pass: nullptr (counts in `in`)
     SumRec* zero;          // input to clear after reading (first pass) or nullptr
     uint32_t* m;           // tour counts to add into MG and clear (first pass) or nullptr
     uint64_t* MG;
     uint32_t rows;
+    uint32_t block;        // rows a block takes (merge_block)
     uint32_t row;
     uint32_t ncols;        // n_max + 1
     uint32_t accumulate;   // final pass: out[n] = out[n] + tree

@@ -2215,8 +2215,8 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(uint32_t* p, size_t word
 // any order) and clears what it read.
 //
 // A small epoch is bound by its launches: 40 sequences take 15.9 us with the
-// counts in a launch of their own, 9.8 us without, and up to 1024
-// sequences are one pass (64 before).
+// counts in a launch of their own, 9.8 us without, and up to 512 sequences are
+// one pass (64 before; merge_block has the figures).
 // ---------------------------------------------------------------------------
 constexpr int MERGE_COLS = 8;
 constexpr int MERGE_WAVES = 16;
@@ -2229,7 +2229,7 @@ __global__ void __launch_bounds__(MERGE_ROWS) merge_pass_kernel(MergeArgs A) {
     const int lane = (int)threadIdx.x & 63;
     const int wave = (int)threadIdx.x >> 6;
     const int waves = (int)blockDim.x >> 6;
-    const uint32_t r = blockIdx.y * MERGE_ROWS + threadIdx.x;
+    const uint32_t r = blockIdx.y * blockDim.x + threadIdx.x;
     const uint32_t c0 = blockIdx.x * MERGE_COLS;
     XF v[MERGE_COLS];
     uint64_t h[MERGE_COLS];
@@ -2274,6 +2274,20 @@ __global__ void __launch_bounds__(MERGE_ROWS) merge_pass_kernel(MergeArgs A) {
             h[j] += __shfl_xor(h[j], lvl, 64);
         }
     }
+    // a column's sum of this block's rows, to its place
+    auto leave = [&](uint32_t c, XF vv, uint64_t hh) INLINE {
+        const size_t o = (size_t)blockIdx.y * A.row + c;
+        if (A.accumulate) {
+            vv = xf_add(xf_of(A.out[o]), vv);
+            if (A.hout) hh += A.hout[o];
+        }
+        SumRec rec;
+        rec.m = vv.m;
+        rec.e = vv.e;
+        rec.h = 0u;
+        A.out[o] = rec;
+        if (A.hout) A.hout[o] = hh;
+    };
     if (lane < MERGE_COLS) {
         // select column `lane` without dynamic register indexing
         XF vv = {0.0, 0};
@@ -2282,12 +2296,22 @@ __global__ void __launch_bounds__(MERGE_ROWS) merge_pass_kernel(MergeArgs A) {
         for (int j = 0; j < MERGE_COLS; ++j) {
             if (j == lane) { vv = v[j]; hh = h[j]; }
         }
-        SumRec rec;
-        rec.m = vv.m;
-        rec.e = vv.e;
-        rec.h = 0u;
-        part[lane * MERGE_WAVES + wave] = rec;
-        parth[lane * MERGE_WAVES + wave] = hh;
+        if (waves == 1) {
+            // (a block of one wave has nothing to add up)
+            if (c0 + (uint32_t)lane < A.ncols) leave(c0 + (uint32_t)lane, vv, hh);
+        } else {
+            SumRec rec;
+            rec.m = vv.m;
+            rec.e = vv.e;
+            rec.h = 0u;
+            part[lane * MERGE_WAVES + wave] = rec;
+            parth[lane * MERGE_WAVES + wave] = hh;
+        }
+    }
+    if (waves == 1) {
+        if (counts && lane == 0)
+            atomicAdd(reinterpret_cast<unsigned long long*>(A.MG), (unsigned long long)t);
+        return;
     }
     __syncthreads();
     if (wave != 0) return;
@@ -2311,19 +2335,7 @@ __global__ void __launch_bounds__(MERGE_ROWS) merge_pass_kernel(MergeArgs A) {
             hh += __shfl_xor(hh, lvl, 64);
         }
         const uint32_t c = c0 + (uint32_t)j;
-        if (w == 0 && c < A.ncols) {
-            const size_t o = (size_t)blockIdx.y * A.row + c;
-            if (A.accumulate) {
-                vv = xf_add(xf_of(A.out[o]), vv);
-                if (A.hout) hh += A.hout[o];
-            }
-            SumRec rec;
-            rec.m = vv.m;
-            rec.e = vv.e;
-            rec.h = 0u;
-            A.out[o] = rec;
-            if (A.hout) A.hout[o] = hh;
-        }
+        if (w == 0 && c < A.ncols) leave(c, vv, hh);
     }
     if (counts && lane == 0) {
         uint64_t all = 0;
@@ -2508,8 +2520,8 @@ hipError_t run_kernel_lds_ok(uint32_t dim, uint32_t team_lanes, uint32_t lds_byt
 }
 
 hipError_t launch_merge_pass(const MergeArgs& a, hipStream_t s) {
-    const uint32_t waves = a.rows < MERGE_ROWS ? (a.rows + 63u) / 64u : (uint32_t)MERGE_WAVES;
-    dim3 grid((a.ncols + MERGE_COLS - 1) / MERGE_COLS, (a.rows + MERGE_ROWS - 1) / MERGE_ROWS);
+    const uint32_t waves = (a.rows < a.block ? a.rows + 63u : a.block) / 64u;
+    dim3 grid((a.ncols + MERGE_COLS - 1) / MERGE_COLS, (a.rows + a.block - 1) / a.block);
     hipLaunchKernelGGL(merge_pass_kernel, grid, dim3(64u * waves), 0, s, a);
     return hipGetLastError();
 }

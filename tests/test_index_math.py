@@ -18,13 +18,16 @@ def lib(tmp_path_factory):
         'extern "C" uint32_t row_of(uint32_t mode, uint32_t s) { return pperm::pooled_row(mode, s); }\n'
         'extern "C" bool digest_word(uint64_t k) { return pperm::is_digest_word(k); }\n'
         'extern "C" uint64_t part(uint32_t dim, uint32_t mode, uint32_t n, uint32_t T)'
-        ' { return pperm::part_tours(dim, mode, n, T); }\n')
+        ' { return pperm::part_tours(dim, mode, n, T); }\n'
+        'extern "C" uint32_t block(uint32_t rows, uint32_t ncols, bool first)'
+        ' { return pperm::merge_block(rows, ncols, first); }\n')
     subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
                     "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "paper_2002_03000_amd", "csrc"),
                     str(d / "w.cpp"), "-o", str(d / "w.so")], check=True, timeout=120)
     lib = ctypes.CDLL(str(d / "w.so"))
     lib.digest_word.argtypes, lib.digest_word.restype = [ctypes.c_uint64], ctypes.c_bool
     lib.part.restype = ctypes.c_uint64
+    lib.block.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_bool]
     return lib
 
 
@@ -53,3 +56,27 @@ def test_a_new_context_seeds_the_digest_of_every_sequence(lib):
 ])
 def test_a_part_has_a_quarter_of_the_tours_or_2048_steps(lib, dim, mode, n_max, tours, part):
     assert lib.part(dim, mode, n_max, tours) == part
+
+
+def test_merge_blocks(lib):
+    # (rows, columns, first pass): the block
+    for args, block in [((1, 2, True), 1024), ((512, 21, True), 1024), ((513, 21, True), 64), ((1000, 51, True), 64),
+                        ((1024, 513, True), 1024), ((1025, 513, True), 64), ((1025, 51, True), 64),
+                        ((4096, 51, True), 64), ((4097, 51, True), 128), ((16384, 21, True), 256),
+                        ((1025, 1600, True), 512), ((16384, 1001, True), 512), ((524288, 2, True), 512),
+                        ((524289, 2, True), 1024), ((1024, 51, False), 1024), ((1025, 51, False), 64)]:
+        assert lib.block(*args) == block, args
+    # every merge ends, takes at most two passes up to 2^20 sequences, and its partial sums
+    # fit the scratch of ceil(N / 64) rows, whatever its size
+    for ncols in (2, 17, 501, 513, 10001, 32767):
+        for N in [2 ** k + d for k in range(32) for d in (-1, 0, 1) if 0 < 2 ** k + d < 2 ** 32]:
+            rows, passes = N, 0
+            while True:
+                block = lib.block(rows, ncols, passes == 0)
+                passes += 1
+                assert 64 <= block <= 1024 and block & (block - 1) == 0
+                if rows <= block:
+                    break
+                rows = -(-rows // block)
+                assert rows <= -(-N // 64)
+            assert passes <= (1 if N <= 512 else 2 if N <= 2 ** 20 else 4), (N, ncols)
