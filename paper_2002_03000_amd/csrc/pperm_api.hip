@@ -228,13 +228,34 @@ int check_device_errors(pperm_ctx* x) {
 // in four copies, 15.7 us in one).  A blocking copy, which also comes after what the
 // default stream and the streams that order with it were given: a chained or batched
 // launch may have run on another stream than the context's.
-int read_pooled(pperm_ctx* x, std::vector<unsigned char>* head) {
-    const uint64_t end = x->lay.ctrl + CTRL_WORDS * 4;
-    head->resize((size_t)(end - x->lay.G));
+struct Pooled {
+    std::vector<unsigned char> part[3];
+    const SumRec* G;
+    const uint64_t* HG;
+    const uint64_t* MG;
+};
+
+int read_pooled(pperm_ctx* x, Pooled* p) {
+    // more than 1 MiB (Algorithm 1's sums): array by array.  A single copy is faster up
+    // to there and slower from there on: 350 sequences of 100 steps (0.94 MB) 432 us in
+    // one, 471 us in three; 500 (1.34 MB) 721 and 663 us
+    const pperm_layout& l = x->lay;
+    const uint64_t end = l.ctrl + CTRL_WORDS * 4;
+    const bool large = end - l.G > (1u << 20);
+    const uint64_t from[] = {l.G, l.HG, l.MG}, to[] = {large ? l.HG : end, l.MG, end};
     if (x->stream != nullptr) HIP_TRY(hipStreamSynchronize(x->stream));
-    HIP_TRY(hipMemcpy(head->data(), at<unsigned char>(x, x->lay.G), head->size(), hipMemcpyDeviceToHost));
+    for (int i = 0; i < (large ? 3 : 1); ++i) {
+        p->part[i].resize((size_t)(to[i] - from[i]));
+        HIP_TRY(hipMemcpy(p->part[i].data(), at<unsigned char>(x, from[i]), p->part[i].size(),
+                          hipMemcpyDeviceToHost));
+    }
+    // (offsets in a part are multiples of 256, a vector's storage is aligned for any type)
+    auto host = [&](int i, uint64_t off) { return p->part[large ? i : 0].data() + (off - (large ? from[i] : l.G)); };
+    p->G = reinterpret_cast<const SumRec*>(host(0, l.G));
+    p->HG = reinterpret_cast<const uint64_t*>(host(1, l.HG));
+    p->MG = reinterpret_cast<const uint64_t*>(host(2, l.MG));
     uint32_t err = 0;
-    memcpy(&err, head->data() + (x->lay.ctrl - x->lay.G) + CTRL_ERR * 4, sizeof(err));
+    memcpy(&err, host(2, l.ctrl) + CTRL_ERR * 4, sizeof(err));
     return note_device_errors(x, err);
 }
 
@@ -1172,13 +1193,12 @@ int pperm_estimates(pperm_ctx* x, double* log_cn, uint64_t* hist, uint64_t* tour
     if (!x || !log_cn) return PPERM_EINVAL;
     const uint32_t n1 = x->cfg.n_max + 1;
     if (len < n1) return PPERM_EINVAL;
-    std::vector<unsigned char> head;
-    int rc = read_pooled(x, &head);
+    Pooled pooled;
+    int rc = read_pooled(x, &pooled);
     if (rc) return rc;
-    // (offsets from G are multiples of 256, the vector's storage is aligned for any type)
-    const SumRec* G = reinterpret_cast<const SumRec*>(head.data());
-    const uint64_t* HG = reinterpret_cast<const uint64_t*>(head.data() + (x->lay.HG - x->lay.G));
-    const uint64_t* MG = reinterpret_cast<const uint64_t*>(head.data() + (x->lay.MG - x->lay.G));
+    const SumRec* G = pooled.G;
+    const uint64_t* HG = pooled.HG;
+    const uint64_t* MG = pooled.MG;
     const uint32_t row = x->lay.row;
     const double ln2 = 0.69314718055994530942;
     if (x->cfg.mode == PPERM_INDEPENDENT) {

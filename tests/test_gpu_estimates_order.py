@@ -25,3 +25,17 @@ def test_estimates_wait_for_a_job_on_the_default_stream(own):
     torch.cuda.synchronize()
     assert_pooled_equal(g, o)
     del scratch
+
+
+@pytest.mark.parametrize("N", [1, 388, 389, 600])
+def test_estimates_of_large_independent_sums(N):
+    # (112 records and counts a sequence: 388 sequences are the last below 1 MiB)
+    g, o = make_pair(2, 100, N, 104, mode="independent")
+    for T in (1, 2):
+        g.run_tours(T)
+        g.merge_epoch()
+        o.run_tours(T)
+        o.merge_epoch()
+    log_cn, hist, tours = g.estimates()
+    assert tours == int(o.MG.sum()) and (hist == o.HG.sum(axis=0)).all()
+    assert abs(log_cn - o.log_estimates()).max() < 1e-9
