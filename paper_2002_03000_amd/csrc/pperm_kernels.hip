@@ -1001,6 +1001,8 @@ constexpr uint32_t WALK_ABORTED = 0x80000000u;
 // hardware's reciprocal has a stated error of 2^29 units in the last place (2^-23),
 // and a uniform's high word is within 2^-20.
 constexpr double DECISION_MARGIN = 0x1p-16;
+// Sites outside their places that are listed, one per lane (a walk has a few at most).
+constexpr uint32_t FAR_LIST = 64;
 
 template <int D, bool OBS = false, bool LONG = false, bool CK = false, bool JOB = false, bool PART = false>
 __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint32_t tours, uint32_t cap,
@@ -1051,7 +1053,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     // At load 0.5 a walk of 1000 cubic steps finds its places all taken about
     // once in 10^4 walks (linear probing over the same lanes: ten times per
     // walk), and 0.65 still costs under 0.3% of its steps; such a site goes into
-    // any empty slot, and far_lo tells the scan to look for it (below).  The
+    // any empty slot, and a list of them tells the events to look there (below).  The
     // last lane of a direction, and the lanes past the directions, read slot
     // S - 1, which no subtable holds (S is 2^b or 3 * 2^b, never a multiple of
     // W - 1) and which stays empty: a free direction has a lane that reads an
@@ -1196,7 +1198,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         uint32_t ra = rec_base + vz, sa = sid_base + vz;
         auto length = [&]() INLINE { return (ufirst(ra) - rec_base) >> 4; };
         Key ekey = origin_key;                 // the walk's end
-        uint32_t far_lo = ~0u;                 // first site of the walk outside its places
+        // sites of the walk outside their places: the first one, and the first
+        // FAR_LIST of them, one per lane, in order (all ones: none)
+        uint32_t far_lo = ~0u, far_at = ~0u;
         // pending copies: sp entries, the one at position p in lane p mod 64
         // of cs for p >= lo, in global memory for p < lo (at
         // most 64 in registers; the most recent ones, which are resumed first)
@@ -1508,14 +1512,21 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 // ---- one event with every case ----
                 uint64_t outside = 0ull;       // directions found outside their places (last lanes)
                 if (far_lo != ~0u) {
-                    for (uint32_t b = far_lo; b <= n; b += 64u) {
-                        const uint32_t i = b + (uint32_t)lane;
-                        const Key k = i <= n ? lds_load<Key>(sid[i] * (uint32_t)sizeof(Key)) : (Key)0;
+                    // (a cubic walk of 10921 steps in 16384 slots has up to three of
+                    // them in its last 1500 steps: 512 Rosenbluth walks of up to that
+                    // length took 7.6 ms with the sites from the first one on searched
+                    // at each event, 3.6 with the list)
+                    auto look = [&](uint32_t i, bool valid) INLINE {
+                        const Key k = valid ? lds_load<Key>(sid[valid ? i : 0u] * (uint32_t)sizeof(Key)) : (Key)0;
                         for (int d = 0; d < 2 * D; ++d)
                             if (__ballot(k == lane_value(nk, (uint32_t)(d * W))) != 0ull &&
                                 ((hits >> (d * W)) & FIELD) == 0ull)
                                 outside |= 1ull << (d * W + W - 1);
-                    }
+                    };
+                    look(far_at, far_at <= n);
+                    // (past a full list the sites themselves are searched)
+                    for (uint32_t b = lane_value(far_at, FAR_LIST - 1u); b < n; b += 64u)
+                        look(b + 1u + (uint32_t)lane, b + 1u + (uint32_t)lane <= n);
                 }
                 const uint32_t au = (uint32_t)(2 * D) - (uint32_t)__popcll(hits | outside);
                 XF w = xf_norm_nz(wm, we);
@@ -1594,6 +1605,8 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                             }
                         }
                         far_lo = min(far_lo, n + 1u);
+                        const uint32_t listed = (uint32_t)__popcll(__ballot(far_at != ~0u));
+                        if ((uint32_t)lane == listed && listed < FAR_LIST) far_at = n + 1u;
                     }
                     digest = (digest ^ ((first >> LW) | (au << 3))) * FNV_PRIME;
                     w = xf_mul_nz(w, (double)au);
@@ -1659,7 +1672,10 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
                 }
                 resume(last_ids());
                 n = length();
-                if (far_lo > n) far_lo = ~0u;
+                if (far_lo != ~0u) {
+                    if (far_at > n) far_at = ~0u;
+                    if (far_lo > n) far_lo = ~0u;
+                }
             }
             arm(n);
         }
