@@ -1163,6 +1163,9 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     double small = -0x1p-501;
     asm volatile("" : "+v"(small));
     const uint32_t lane2 = 2u * (uint32_t)lane;
+    // (LONG) the longest walk so far, as the address of its slot id: a row's records
+    // past it are as they were
+    uint32_t longest = sid_base + vz;
 
     for (uint32_t tour = 0; tour < tours && !abort; ++tour) {
         // ---- a pass through the empty walk (eqn (4), M) ----
@@ -1411,6 +1414,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
             const uint32_t rem = lane_value(cs.rem, tl);
             // LIFO deletion of the sites after it restores the table exactly
             const uint32_t end = sa;
+            if constexpr (LONG) longest = max(longest, end);
             sa = (ra >> 3) + (sid_base - rec_base / 8u);
             clear_sites_take_copy<Key>(lane2, end - sa, at * (uint32_t)sizeof(Key), cs.rem, tl);
             if (__builtin_expect(__ballot(end - sa > 128u) != 0ull, 0)) {
@@ -1681,6 +1685,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
         }
         // end of the tour (or abort): back to the empty walk
         c_events += kb + li - 1u;
+        if constexpr (LONG) longest = max(longest, sa);
         const uint32_t n = length();
         for (uint32_t i = 1u + (uint32_t)lane; i <= n; i += 64u) clear_id(sid[i]);
         wave_fence();
@@ -1688,7 +1693,10 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     // (read again, so that the steps need not keep what only the end uses)
     asm volatile("" : "+s"(desc));
     const ProblemDesc Q = load_const(desc);
-    // the sums leave normalised (m in [0.5, 1), or 0 with e = 0)
+    // the sums leave normalised (m in [0.5, 1), or 0 with e = 0); with LONG those of
+    // the lengths that were reached (4096 square Rosenbluth walks of up to 16383 steps,
+    // trapped after 71 on average: 2.41 ms a tour with whole rows, 0.49 with this)
+    const uint32_t reached = LONG ? (ufirst(longest) - sid_base) / 2u : Q.n_max;
     auto leave = [&](SumRec* p, SumRec* out) INLINE {
         SumRec r = rec_ld(p);
         const XF v = xf_norm(r.m, r.e);
@@ -1701,7 +1709,7 @@ __device__ __forceinline__ uint32_t walk_sequence(const ProblemDesc* desc, uint3
     if (lane == 0) rec_st(Ls, rec0);
     wave_fence();
 #pragma unroll 1
-    for (uint32_t i = (uint32_t)lane; i <= Q.n_max; i += 64u) {
+    for (uint32_t i = (uint32_t)lane; i <= reached; i += 64u) {
         leave(Ls + i, Q.L + (size_t)s * Q.row + i);
         if constexpr (OBS) leave(LRs + i, Q.LR + (size_t)s * Q.row + i);
     }

@@ -16,3 +16,23 @@ def test_full_tables_match_oracle(n_max, N, kw):
         o.run_tours(T)
         assert_epoch_equal(g, o, label=f"n_max={n_max}")
     assert int(o.H[:, n_max].sum()) > 0                 # (some walks have the full length)
+
+
+@pytest.mark.parametrize("dim,n_max,N,kw", [(2, 16383, 40, {}), (3, 300, 200, dict(sums_global=True)),
+                                            (2, 2000, 60, dict(sums_global=True, observables=True))])
+def test_long_rows_leave_normalised(dim, n_max, N, kw):
+    # (only the lengths a call reached are written back; the next call reaches others)
+    import numpy as np
+    import oracle
+    from paper_2002_03000_amd import ParallelFlatPERM
+    g = ParallelFlatPERM(dim, n_max, N, 105, mode="rosenbluth", **kw)
+    o = oracle.Oracle(dim, n_max, N, 105, mode=oracle.MODE_ROSENBLUTH, observables=kw.get("observables", False))
+    for T in (1, 1, 3):
+        g.run_tours(T)
+        o.run_tours(T)
+        assert_epoch_equal(g, o, label=f"n_max={n_max} T={T}")
+    g.merge_epoch()
+    o.merge_epoch()
+    if kw.get("observables"):
+        rec = g.records("obs_G")[: n_max + 1]
+        assert np.array_equal(rec["m"], o.GR["m"]) and np.array_equal(rec["e"], o.GR["e"])
