@@ -139,12 +139,20 @@ constexpr uint64_t tour_steps(uint32_t dim, uint32_t mode, uint32_t n_max) {
 }
 
 // Tours of a part: a quarter of the call's, or more where that is under 2048 steps
-// (about 0.5 ms; a hand-over takes some 20 us and, in a long row, more: square
-// Rosenbluth walks of up to 2000 steps, 4400 sequences of 8 tours on 2048 waves,
-// take 0.74 ms in parts of 142 steps and 0.41 ms whole).
+// (about 0.5 ms; a hand-over takes some 20 us and moves the row, 7 ns a length).
+// Square walks that are trapped long before n_max differ little, so that there is
+// nothing to even out, and their rows are long against their steps: four rows'
+// lengths of steps at least.  Rosenbluth walks of 64 tours, ms, in parts of 2048
+// steps / as chosen here:
+//   square, n_max 500, 8000 on 3072 waves      2.87 / 2.87   (whole: 3.07)
+//   square, n_max 2000, 8192 on 2048 waves     4.17 / 3.78   (whole)
+//   square, n_max 16383, 4096 on 256 waves     17.1 / 11.7   (whole)
+//   cubic, n_max 6000, 4 tours, 1000 on 256    9.19 / 9.19   (whole: 9.69)
 constexpr uint64_t part_tours(uint32_t dim, uint32_t mode, uint32_t n_max, uint32_t tours) {
     const uint64_t steps = tour_steps(dim, mode, n_max);
-    const uint64_t quarter = ((uint64_t)tours + PART_MAX - 1u) / PART_MAX, least = (2048ull + steps - 1ull) / steps;
+    const uint64_t rows = dim == 2u && steps <= n_max ? 4ull * (n_max + 1ull) : 0ull;
+    const uint64_t least_steps = rows > 2048ull ? rows : 2048ull;
+    const uint64_t quarter = ((uint64_t)tours + PART_MAX - 1u) / PART_MAX, least = (least_steps + steps - 1ull) / steps;
     return quarter > least ? quarter : least;
 }
 

@@ -58,7 +58,8 @@ def test_short_rosenbluth_tours_stay_whole():
     g = ParallelFlatPERM(2, 2000, 4400, 100, mode="rosenbluth", sums_global=True)
     assert g.launch_shape()["workgroups"] < 4400
     assert _hand_overs(g, 8) is None
-    assert _hand_overs(g, 64) == 2 * 4400                # (parts of 29 tours)
+    assert _hand_overs(g, 64) is None
+    assert _hand_overs(g, 200) == 4400                   # (parts of 113 tours)
 
 
 def test_as_many_tours_as_a_call_may_ask_for():

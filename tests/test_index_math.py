@@ -48,8 +48,9 @@ def test_a_new_context_seeds_the_digest_of_every_sequence(lib):
 @pytest.mark.parametrize("dim,mode,n_max,tours,part", [
     (2, SHARED, 500, 64, 16), (3, SHARED, 1000, 32, 8), (2, SHARED, 127, 33, 16), (2, SHARED, 1, 4096, 1024),
     (3, INDEPENDENT, 255, 17, 8),
-    # a trapped walk's steps, not n_max: 2048 / 71 = 28.8, and 2048 / 3950 < 1
-    (2, ROSENBLUTH, 2000, 8, 29), (2, ROSENBLUTH, 500, 200, 50), (2, ROSENBLUTH, 60, 8, 34),
+    # a trapped walk's steps, not n_max: 2048 / 71 = 28.8, and 2048 / 3950 < 1;
+    # on the square lattice four rows of them: 4 * 2001 / 71 = 112.7
+    (2, ROSENBLUTH, 500, 8, 29), (2, ROSENBLUTH, 2000, 8, 113), (2, ROSENBLUTH, 16383, 256, 924), (2, ROSENBLUTH, 500, 200, 50), (2, ROSENBLUTH, 60, 8, 34),
     (3, ROSENBLUTH, 700, 9, 3), (3, ROSENBLUTH, 9000, 3, 1),
     # as many tours as a call may ask for
     (3, INDEPENDENT, 2, 2 ** 32 - 1, 2 ** 30), (2, ROSENBLUTH, 5000, 2 ** 32 - 4, 2 ** 30 - 1),
