@@ -174,16 +174,19 @@ struct PartArgs {
 //   1000 sequences of 1000 steps   24.3 / 27.8 / 24.3
 //   4096                             72 /   75 /   64
 //   16384                           222 /  205 /  162
+//   1000 sequences of 10000 steps   174 /  135 /  135   (512: 121, and 149 for 1065)
 constexpr uint32_t MERGE_ROWS = 1024;
 constexpr uint32_t merge_block(uint32_t rows, uint32_t ncols, bool first) {
+    const uint64_t records = (uint64_t)rows * ncols;
+    const bool most = records >= 1u << 22;     // their reading is most of the time
     // one block: up to 512 rows, or up to 1024 where there are columns enough to fill
     // the chip, or where the rows are sums of others already
-    if (rows <= 512u || (rows <= MERGE_ROWS && (!first || ncols > 512u))) return MERGE_ROWS;
+    if (rows <= 512u || (rows <= MERGE_ROWS && (!first || (ncols > 512u && !most)))) return MERGE_ROWS;
     // two passes, not three
     if (rows > 512u * MERGE_ROWS) return MERGE_ROWS;
-    // many records: their reading counts, not the second pass
-    if ((uint64_t)rows * ncols >= 3u << 19) return 512u;
-    // few: one wave's rows are left for the second pass
+    // many records, and blocks enough that the last, short one does not matter
+    if (records >= 3u << 19 && !(most && rows < 1280u)) return 512u;
+    // else one wave's rows are left for the second pass
     uint32_t block = 64u;
     while (block < 512u && 64u * block < rows) block *= 2u;
     return block;

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_max,N,kw", [
     (9, 512, {}), (9, 513, {}), (9, 4096, {}), (9, 4097, {}), (9, 8193, dict(observables=True)), (9, 20001, {}),
-    (600, 700, {}), (600, 1024, dict(observables=True)), (600, 1030, {}), (1100, 1500, {}),
+    (5000, 900, {}), (600, 700, {}), (600, 1024, dict(observables=True)), (600, 1030, {}), (1100, 1500, {}),
     (2, 524289, {}), (1, 1100000, {}),
 ])
 def test_merge_blocks_match_oracle(n_max, N, kw):

@@ -65,7 +65,9 @@ def test_merge_blocks(lib):
                         ((1024, 513, True), 1024), ((1025, 513, True), 64), ((1025, 51, True), 64),
                         ((4096, 51, True), 64), ((4097, 51, True), 128), ((16384, 21, True), 256),
                         ((1025, 1600, True), 512), ((16384, 1001, True), 512), ((524288, 2, True), 512),
-                        ((524289, 2, True), 1024), ((1024, 51, False), 1024), ((1025, 51, False), 64)]:
+                        ((524289, 2, True), 1024), ((1024, 51, False), 1024), ((1025, 51, False), 64),
+                        ((700, 5001, True), 1024), ((1000, 5001, True), 64), ((1065, 2501, True), 512),
+                        ((1279, 10001, True), 64), ((1280, 10001, True), 512), ((1000, 10001, False), 1024)]:
         assert lib.block(*args) == block, args
     # every merge ends, takes at most two passes up to 2^20 sequences, and its partial sums
     # fit the scratch of ceil(N / 64) rows, whatever its size
