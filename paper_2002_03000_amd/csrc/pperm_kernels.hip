@@ -991,10 +991,10 @@ __device__ __forceinline__ void put_entry(CopyLanes<Key>& c, uint32_t p, uint32_
 // handled outside, in the extended-range form (the event loop).
 // Measured with every case decided in line (255 instructions and 17 branches a
 // step) / now, ms, means of three seeds:
-//   one square sequence of 20-step walks, 1000 tours      12.4 / 5.02
-//   4096 square sequences of 500 steps, 64 tours          77.3 / 28.8
-//   16384 cubic sequences of 1000 steps, 32 tours          163 / 68.8
-//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.42 / 1.93
+//   one square sequence of 20-step walks, 1000 tours      12.4 / 5.05
+//   4096 square sequences of 500 steps, 64 tours          77.1 / 29.0
+//   16384 cubic sequences of 1000 steps, 32 tours          164 / 68.9
+//   256 Rosenbluth walks of up to 6000 cubic steps, twice 6.41 / 1.93
 // A lone wave's step (us): square 0.625 / 0.222, cubic 0.610 / 0.205.
 constexpr uint32_t WALK_ABORTED = 0x80000000u;
 // run_ahead's distance from a decision that the rounding of r could change: the
